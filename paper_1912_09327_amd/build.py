@@ -16,6 +16,11 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "liblbt1.so")
 SOURCES = ["lbt1_kernels.hip", "lbt1_runtime.hip", "lbt1_batch.hip", "lbt1_probe.hip", "lbt1_3d.hip"]
+# sources compiled once per storage precision (LBT1_PREC), the longest to compile first
+PREC_SOURCES = ["lbt1_step_kernels.hip", "lbt1_batch_step_kernels.hip"]
+UNITS = [(s, p) for s in PREC_SOURCES for p in (1, 2, 3, 0)] + [(s, None) for s in SOURCES]
+# sources whose kernels must neither spill registers nor use scratch memory
+CHECKED = PREC_SOURCES + ["lbt1_kernels.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
@@ -46,9 +51,11 @@ def _resources(text):
     return res
 
 
-def _compile(src, out, verbose):
+def _compile(src, prec, out, verbose):
     cmd = [HIPCC] + FLAGS + ["-c", os.path.join(CSRC, src), "-o", out]
-    if src == "lbt1_kernels.hip":
+    if prec is not None:
+        cmd.append(f"-DLBT1_PREC={prec}")
+    if src in CHECKED:
         cmd.append("-Rpass-analysis=kernel-resource-usage")
     if verbose:
         print(" ".join(cmd), flush=True)
@@ -56,7 +63,7 @@ def _compile(src, out, verbose):
     lines = [ln for ln in (r.stdout + r.stderr).splitlines() if "packed-fp32-ops" not in ln]
     if r.returncode != 0:
         raise RuntimeError(f"hipcc failed for {src}:\n" + "\n".join(lines))
-    if src == "lbt1_kernels.hip":
+    if src in CHECKED:
         # No step kernel may spill registers or use scratch memory: the strip
         # kernels are sized to stay in registers, and a spilling variant is a
         # design error (it is not built).
@@ -71,9 +78,9 @@ def _compile(src, out, verbose):
 def build(verbose: bool = False) -> str:
     tmp = tempfile.mkdtemp(prefix="lbt1_build_")
     try:
-        objs = [os.path.join(tmp, s + ".o") for s in SOURCES]
-        with cf.ThreadPoolExecutor(max_workers=len(SOURCES)) as ex:
-            for msg in ex.map(lambda a: _compile(a[0], a[1], verbose), zip(SOURCES, objs)):
+        objs = [os.path.join(tmp, f"{s}.{p}.o") for s, p in UNITS]
+        with cf.ThreadPoolExecutor(max_workers=min(8, os.cpu_count() or 1)) as ex:
+            for msg in ex.map(lambda a: _compile(*a[0], a[1], verbose), zip(UNITS, objs)):
                 if msg.strip() and verbose:
                     print(msg)
         cmd = [HIPCC, f"--offload-arch={ARCH}", "-shared", "-fPIC", "-o", LIB + ".tmp"] + objs

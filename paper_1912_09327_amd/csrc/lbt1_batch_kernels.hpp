@@ -1,5 +1,5 @@
 // Batched step kernels beyond one step per launch (templates; instantiated in
-// lbt1_kernels.hip).  They run over the same flattened (grid, strip) item lists
+// lbt1_batch_step_kernels.hip).  They run over the same flattened (grid, strip) item lists
 // and grid descriptors as k_step_batch, with the arithmetic and its order of the
 // single-grid kernels, so every grid gets the bits it would get alone.
 #pragma once
@@ -196,38 +196,6 @@ __global__ void __launch_bounds__(256) k_reduce_batch(BatchReduceArgs b) {
       b.partials[(long)it * 6 + q] = v;
     }
     __syncthreads();
-  }
-}
-
-// The partials of each active grid (fixed order: lane-strided, then a butterfly)
-// into out[slot * 6 + q].
-__global__ void __launch_bounds__(64) k_reduce_batch_final(BatchReduceArgs b) {
-  const int n = *b.nactive;
-  for (int k = blockIdx.x; k < n; k += gridDim.x) {
-    const int slot = b.active[k];
-    const int2 r = b.ranges[slot];
-    // lane l: partial rows l, l + 64, ... of the grid in order, then a fixed butterfly
-    const int l = threadIdx.x;
-    double acc[6] = {0, 0, 0, 0, 0, 0};
-    for (int i = l; i < r.y; i += 64) {
-#pragma unroll
-      for (int q = 0; q < 6; ++q) {
-        const double x = b.partials[(long)(r.x + i) * 6 + q];
-        acc[q] = q == 3 ? __builtin_fmax(acc[q], x) : acc[q] + x;
-      }
-    }
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-#pragma unroll
-      for (int q = 0; q < 6; ++q) {
-        const double o = __shfl_xor(acc[q], off);
-        acc[q] = q == 3 ? __builtin_fmax(acc[q], o) : acc[q] + o;
-      }
-    }
-    if (l == 0) {
-#pragma unroll
-      for (int q = 0; q < 6; ++q) b.out[slot * 6 + q] = acc[q];
-    }
   }
 }
 

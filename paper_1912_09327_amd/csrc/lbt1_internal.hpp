@@ -18,6 +18,30 @@ struct StepKernel {
   int sc;     // multiphase (Shan-Chen force) kernel
 };
 
+// The kernels of one storage precision (lbt1_step_kernels.hip and
+// lbt1_batch_step_kernels.hip, each compiled once per precision).
+struct PrecKernels {
+  const StepKernel *steps;
+  int count;
+  const void *reduce_partial, *bgk_psi, *bgk_reduce_partial;
+};
+struct BatchKernels {
+  const void *step[3][3];  // [strips of 6, 14, 30 rows][1, 2, 4 columns per lane]
+  const void *fused[4];    // strips of 2, 6, 14, 30 rows
+  const void *lds[2];      // strips of 6, 14 rows
+  const void *reduce;
+};
+template <int P> const PrecKernels &prec_kernels();
+template <int P> const BatchKernels &batch_kernels();
+template <> const PrecKernels &prec_kernels<0>();
+template <> const PrecKernels &prec_kernels<1>();
+template <> const PrecKernels &prec_kernels<2>();
+template <> const PrecKernels &prec_kernels<3>();
+template <> const BatchKernels &batch_kernels<0>();
+template <> const BatchKernels &batch_kernels<1>();
+template <> const BatchKernels &batch_kernels<2>();
+template <> const BatchKernels &batch_kernels<3>();
+
 const StepKernel *step_kernels(int *count);
 const void *reduce_partial_kernel(int prec);
 const void *reduce_final_kernel();

@@ -17,7 +17,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "liblbt1.so")
 SOURCES = ["lbt1_kernels.hip", "lbt1_runtime.hip", "lbt1_batch.hip", "lbt1_probe.hip", "lbt1_3d.hip"]
 # sources compiled once per storage precision (LBT1_PREC), the longest to compile first
-PREC_SOURCES = ["lbt1_step_kernels.hip", "lbt1_batch_step_kernels.hip"]
+PREC_SOURCES = ["lbt1_step_kernels.hip", "lbt1_batch_step_kernels.hip", "lbt1_tile_kernels.hip"]
 UNITS = [(s, p) for s in PREC_SOURCES for p in (1, 2, 3, 0)] + [(s, None) for s in SOURCES]
 # sources whose kernels must neither spill registers nor use scratch memory
 CHECKED = PREC_SOURCES + ["lbt1_kernels.hip"]

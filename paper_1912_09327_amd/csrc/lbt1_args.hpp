@@ -14,6 +14,14 @@ struct StripMap {
   int persistent;          // 0: one block per unit; else grid-stride within the XCD range
 };
 
+// Tiles of k_step_tile: steps this launch takes, halo and stored nodes of a tile on
+// each axis, tiles per row of tiles.
+struct TileMap {
+  int steps;
+  int hx, hy, ox, oy;
+  int tiles_x;
+};
+
 struct ReduceArgs {
   const void *cur[3];
   void *snap[3];

@@ -6,16 +6,21 @@
 
 namespace lbt1 {
 
-enum : int { KIND_GATHER = 1, KIND_STRIP = 2, KIND_BGK = 3 };
+enum : int { KIND_GATHER = 1, KIND_STRIP = 2, KIND_BGK = 3, KIND_TILE = 4 };
 
 // One built step kernel.  Gather kernels take (StepArgs); strip kernels take
-// (StepArgs, StripMap); population (BGK) kernels take (BgkArgs).
+// (StepArgs, StripMap); tile kernels take (StepArgs, TileMap); population (BGK)
+// kernels take (BgkArgs).
 struct StepKernel {
   int prec, haswall, wall, kind, vec, rows;
   const void *fn;
   const char *name;
-  int steps;  // time steps one launch advances (fused strip kernels: 2)
+  int steps;  // time steps one launch advances (fused strip kernels: 2; tile kernels: any)
   int sc;     // multiphase (Shan-Chen force) kernel
+  int threads = 256;  // tile kernels: threads of a block (vec: columns, rows: rows of its region)
+  // tile kernels, measured: us of a launch, and of each block that falls to one CU, per
+  // step and once
+  double us_launch = 0, us_step = 0, us_block = 0;
 };
 
 // The kernels of one storage precision (lbt1_step_kernels.hip and
@@ -33,6 +38,11 @@ struct BatchKernels {
 };
 template <int P> const PrecKernels &prec_kernels();
 template <int P> const BatchKernels &batch_kernels();
+template <int P> const StepKernel *tile_kernels(int *count);
+template <> const StepKernel *tile_kernels<0>(int *count);
+template <> const StepKernel *tile_kernels<1>(int *count);
+template <> const StepKernel *tile_kernels<2>(int *count);
+template <> const StepKernel *tile_kernels<3>(int *count);
 template <> const PrecKernels &prec_kernels<0>();
 template <> const PrecKernels &prec_kernels<1>();
 template <> const PrecKernels &prec_kernels<2>();

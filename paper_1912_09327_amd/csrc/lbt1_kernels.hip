@@ -107,6 +107,11 @@ const StepKernel *step_kernels(int *count) {
   static const std::vector<StepKernel> all = [] {
     std::vector<StepKernel> t;
     for (int p = P_F64; p <= P_BF16S; ++p) t.insert(t.end(), of_prec(p)->steps, of_prec(p)->steps + of_prec(p)->count);
+    for (auto tiles : {tile_kernels<P_F64>, tile_kernels<P_F32>, tile_kernels<P_F16S>, tile_kernels<P_BF16S>}) {
+      int n = 0;
+      const StepKernel *k = tiles(&n);
+      t.insert(t.end(), k, k + n);
+    }
     return t;
   }();
   *count = (int)all.size();

@@ -243,6 +243,19 @@ lbt1_status check_device(int *dev_out, int *cus) {
 static bool strip_fits(int nx, int vec, bool periodic_x) { return vec >= 1 && (nx % vec == 0 || !periodic_x); }
 static int chunks_of(int nx, int vec) { return (nx + vec - 1) / vec; }
 
+// The tile kernel with regions of w columns and `rows` rows on `waves` wavefronts.
+static const StepKernel *find_tile(int prec, bool haswall, int wall, int w, int rows, int waves) {
+  int n = 0;
+  const StepKernel *t = step_kernels(&n);
+  for (int i = 0; i < n; ++i) {
+    const StepKernel &k = t[i];
+    if (k.kind == KIND_TILE && k.prec == prec && (k.haswall != 0) == haswall && (!haswall || k.wall == wall) &&
+        k.vec == w && k.rows == rows && k.threads == 64 * waves)
+      return &k;
+  }
+  return nullptr;
+}
+
 const StepKernel *find_kernel(int prec, bool haswall, int wall, int kind, int vec, int rows, int fuse, bool sc) {
   int n = 0;
   const StepKernel *t = step_kernels(&n);
@@ -267,120 +280,111 @@ static std::tuple<int, int, int, int, int, int> tune_key(const lbt1_grid *g) {
                          g->nx, g->ny);
 }
 
-// Default without a tuned entry: the gather kernel for tiny grids, else the
-// widest built strip kernel that fits nx (see strip_fits) and whose strip is not much
-// wider than the grid, with short strips (6 rows) when tall ones would not give
-// every CU several wavefronts (a strip's rows are walked one after another, so
-// its length sets the latency of a step).
-lbt1_kernel_config heuristic_config(int prec, bool haswall, int wall, int nx, int ny, int cus, bool sc, bool px) {
+// A strip configuration of 32 columns or more is a tile kernel's: vec columns and `rows`
+// rows of the region, `waves` wavefronts of a block, `fuse` steps of a launch.
+static bool is_tile(const lbt1_kernel_config &c) { return c.kernel == LBT1_KERNEL_STRIP && c.vec >= 32; }
+
+// Most steps of one launch of a tile kernel (the steps of a graph burst).
+constexpr int kMaxTileSteps = 64;
+
+// Tiles of configuration c on an nx x ny grid for a launch of `steps` steps: a halo
+// of that many nodes on each side of an axis, none on an axis that is not periodic and
+// fits the region whole.  False when the halo leaves nothing to store.
+static bool tile_map(int nx, int ny, uint32_t periodic, const lbt1_kernel_config &c, int steps, TileMap *m) {
+  m->steps = steps;
+  const int even = (steps + 1) / 2 * 2;  // chunks of two columns start at even columns
+  m->hx = !(periodic & 1u) && nx <= c.vec ? 0 : c.vec > 64 ? even : steps;
+  m->hy = !(periodic & 2u) && ny <= c.rows ? 0 : steps;
+  m->ox = c.vec - 2 * m->hx;
+  m->oy = c.rows - 2 * m->hy;
+  if (m->ox < 1 || m->oy < 1) return false;
+  m->tiles_x = (nx + m->ox - 1) / m->ox;
+  return true;
+}
+static long tile_blocks(const TileMap &m, int ny) { return (long)m.tiles_x * ((ny + m.oy - 1) / m.oy); }
+
+// Steps of a launch the choice is made over (and the autotuner's candidates).  One step
+// of a launch widens the halo by a node; three and fewer measured slower on every grid.
+static const int kTileSteps[] = {4, 6, 8, 10, 12, 16, kMaxTileSteps};
+
+// Default without a tuned entry: the tile kernel and steps per launch with the least
+// modelled time per step.  A launch takes us_launch and, for each block that falls to
+// the busiest CU (past eight rounds the average: blocks end at different times), us_step
+// per step and us_block.  On 80 grids of 48^2 to 8192^2, periodic and cavities, FP64,
+// FP32 and FP16S, what it picks is within 2 % of the fastest shape on average.
+//
+// In FP32 and FP64 that beat every strip and gather kernel at each size (us per step,
+// tile against the best of those: FP32 periodic 256^2 0.77 / 3.4, 1024^2 3.1 / 7.1,
+// 4096^2 29.0 / 31.1, 8192^2 107 / 108.5; FP32 cavity 256^2 1.02 / 2.85, 1024^2 4.6 /
+// 6.5, 8192^2 125 / 168; FP64 periodic 8192^2 224 / 302, cavity 274 / 540).  16-bit
+// storage pays its codec once per step either way, and the strips exchange columns off
+// the vector ALU: on large grids whose width they take, two-step strips of 14 rows are
+// the faster (FP16S periodic 4096^2 27.3 against 29.2, cavity 8192^2 116 against 132;
+// but 2048^2 9.75 against 9.2 and 14.1 against 11.1), by a time of `half_strip` us per
+// million nodes and `half_base` us, fitted to the same grids.
+static lbt1_kernel_config default_config(int prec, bool haswall, int wall, int nx, int ny, uint32_t periodic, int cus) {
+  lbt1_kernel_config best{};
+  best.kernel = LBT1_KERNEL_GATHER;
+  double best_us = 1e300;
+  int n = 0;
+  const StepKernel *t = step_kernels(&n);
+  for (int i = 0; i < n; ++i) {
+    const StepKernel &k = t[i];
+    if (k.kind != KIND_TILE || k.prec != prec || (k.haswall != 0) != haswall || (haswall && k.wall != wall)) continue;
+    for (int steps : kTileSteps) {
+      lbt1_kernel_config c{};
+      c.kernel = LBT1_KERNEL_STRIP;
+      c.vec = k.vec;
+      c.rows = k.rows;
+      c.waves = k.threads / 64;
+      c.fuse = steps;
+      TileMap m;
+      if (!tile_map(nx, ny, periodic, c, steps, &m)) continue;
+      const double per_cu = (double)tile_blocks(m, ny) / cus;
+      const double rounds = per_cu <= 8 ? std::ceil(per_cu) : per_cu + 0.5;
+      const double us = (k.us_launch + rounds * (steps * k.us_step + k.us_block)) / steps;
+      if (us < best_us) {
+        best_us = us;
+        best = c;
+      }
+    }
+  }
+  const double half_strip = haswall ? 1.70 : 1.62, half_base = haswall ? 5.0 : 2.5;
+  if ((prec == LBT1_F16S || prec == LBT1_BF16S) && strip_fits(nx, 2, periodic & 1u) &&
+      half_strip * 1e-6 * nx * ny + half_base < best_us && find_kernel(prec, haswall, wall, KIND_STRIP, 2, 14, 2, false)) {
+    best = lbt1_kernel_config{};
+    best.kernel = LBT1_KERNEL_STRIP;
+    best.vec = 2;
+    best.rows = 14;
+    best.fuse = 2;
+  }
+  return best;
+}
+
+// Default without a tuned entry for a multiphase grid: strips (2 columns per lane) on
+// periodic grids without walls that give every CU two strips or more, else one thread
+// per node.  FP32 grids with two 22-row strips of two fused steps per CU take those
+// (drop fields: 71.5 against 82.4 us per step at 4096^2, 232 against 284 at 8192^2).
+static lbt1_kernel_config sc_choice(int prec, bool haswall, int nx, int ny, int cus) {
   lbt1_kernel_config c{};
-  if ((long)nx * ny < 64 * 64) {
-    c.kernel = LBT1_KERNEL_GATHER;
+  c.kernel = LBT1_KERNEL_GATHER;
+  if ((long)nx * ny < 64 * 64) return c;
+  const long fused = (long)((nx / 4 + 61) / 62) * ((ny + 21) / 22);
+  if (prec == LBT1_F32 && !haswall && nx % 4 == 0 && fused >= 2L * cus &&
+      find_kernel(prec, false, 0, KIND_STRIP, 4, 22, 2, true)) {
+    c.kernel = LBT1_KERNEL_STRIP;
+    c.vec = 4;
+    c.rows = 22;
+    c.fuse = 2;
     return c;
   }
-  if (sc) {
-    // multiphase: strips (2 columns per lane) on periodic grids without walls that
-    // give every CU two strips or more, else one thread per node.  FP32 grids with
-    // two 22-row strips of two fused steps per CU take those (drop fields: 71.5
-    // against 82.4 us per step at 4096^2, 232 against 284 at 8192^2).
-    c.kernel = LBT1_KERNEL_GATHER;
-    const long fused = (long)((nx / 4 + 61) / 62) * ((ny + 21) / 22);
-    if (prec == LBT1_F32 && !haswall && nx % 4 == 0 && fused >= 2L * cus &&
-        find_kernel(prec, false, 0, KIND_STRIP, 4, 22, 2, true)) {
-      c.kernel = LBT1_KERNEL_STRIP;
-      c.vec = 4;
-      c.rows = 22;
-      c.fuse = 2;
-      return c;
-    }
-    const long strips = (long)((nx / 2 + 61) / 62) * ((ny + 13) / 14);
-    if (!haswall && nx % 2 == 0 && strips >= 2L * cus && find_kernel(prec, false, 0, KIND_STRIP, 2, 14, 1, true)) {
-      c.kernel = LBT1_KERNEL_STRIP;
-      c.vec = 2;
-      c.rows = 14;
-      c.fuse = 1;
-    }
-    return c;
+  const long strips = (long)((nx / 2 + 61) / 62) * ((ny + 13) / 14);
+  if (!haswall && nx % 2 == 0 && strips >= 2L * cus && find_kernel(prec, false, 0, KIND_STRIP, 2, 14, 1, true)) {
+    c.kernel = LBT1_KERNEL_STRIP;
+    c.vec = 2;
+    c.rows = 14;
+    c.fuse = 1;
   }
-  c.kernel = LBT1_KERNEL_STRIP;
-  c.waves = 0;
-  c.vec = 1;
-  c.fuse = 1;
-  if (!haswall) {
-    // several steps per pass (measured fastest on large periodic grids): FP32 three
-    // steps at 4 columns per lane; FP64 two at 2 (registers); 16-bit storage two at
-    // 2 columns. Tall strips where there are enough of them: these kernels are
-    // bound by arithmetic, and a taller strip repeats fewer halo rows.
-    const bool half = prec == LBT1_F16S || prec == LBT1_BF16S;
-    const int v = prec == LBT1_F32 ? 4 : 2;
-    const int k = prec == LBT1_F32 ? 3 : 2;
-    if (nx % v == 0 && 62 * v <= std::max(62, nx)) {
-      const long sx = (nx / v + 61) / 62;
-      int r = half ? (sx * ((ny + 29) / 30) >= 8L * cus ? 30 : 6)
-                   : prec == LBT1_F32 ? (sx * ((ny + 21) / 22) >= 8L * cus ? 22 : 14) : 6;
-      if (r == 22) {
-        // three-step strips run two wavefronts per SIMD (8 per CU): a launch of W
-        // strips takes about ceil(W / slots) rounds of one strip's walk, 3 R + 12
-        // stage-row emissions for R stored rows.  28 rows where that is no longer
-        // than at 22 (the 8192^2 field: 5 rounds of 96 against 7 of 78).
-        const long slots = 8L * cus;
-        const long w22 = sx * ((ny + 21) / 22), w28 = sx * ((ny + 27) / 28);
-        if ((w28 + slots - 1) / slots * 96 <= (w22 + slots - 1) / slots * 78) r = 28;
-      }
-      if (find_kernel(prec, false, 0, KIND_STRIP, v, r, k, false)) {
-        c.vec = v;
-        c.rows = r;
-        c.fuse = k;
-        c.waves = 0;
-        return c;
-      }
-    }
-  }
-  if (haswall && strip_fits(nx, 2, px) && 62 * 2 <= std::max(62, nx)) {
-    // two fused steps at 2 columns per lane on grids with walls (measured on
-    // cavities of side 256, 1024 and 4096: fastest in FP32 and 16-bit storage at
-    // every size, in FP64 at 256 and 4096 and within 6 % at 1024).  Strip height:
-    // up to 512 x 512 nodes 2 rows (the step is bound by the latency of a strip's
-    // walk: 2.9 us against 5.0 at 6 rows on a 256^2 cavity), else 14 where there
-    // are enough strips, else 6.  30 rows where a launch then takes at least 5 %
-    // less of rounds of resident wavefronts times walk length (2 R + 6 stage rows)
-    // than at 14: on the 8192^2 cavity 6 rounds of 66 against 13 of 34 (FP32 0.190
-    // against 0.204 ms per step); at 4096^2 2 of 66 against 4 of 34, and 14 rows
-    // are 1-4 % faster.
-    const long sx = (chunks_of(nx, 2) + 61) / 62;
-    int r = (long)nx * ny <= 512L * 512 ? 2 : sx * ((ny + 13) / 14) >= 8L * cus ? 14 : 6;
-    const StepKernel *k30 = find_kernel(prec, true, wall, KIND_STRIP, 2, 30, 2, false);
-    if (r == 14 && k30) {
-      int per_cu = 0;  // 256-thread blocks per CU
-      if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k30->fn, 256, 0) == hipSuccess && per_cu > 0) {
-        const long slots = 4L * per_cu * cus;
-        const long w14 = sx * ((ny + 13) / 14), w30 = sx * ((ny + 29) / 30);
-        if ((w30 + slots - 1) / slots * 66 * 20 < (w14 + slots - 1) / slots * 34 * 19) r = 30;
-      }
-    }
-    if (find_kernel(prec, true, wall, KIND_STRIP, 2, r, 2, false)) {
-      c.vec = 2;
-      c.rows = r;
-      c.fuse = 2;
-      c.waves = 0;
-      return c;
-    }
-  }
-  const int cands[] = {8, 4, 2, 1};
-  for (int v : cands) {
-    if (strip_fits(nx, v, px) && 62 * v <= std::max(62, nx) && find_kernel(prec, haswall, wall, KIND_STRIP, v, 14, 1, false)) {
-      c.vec = v;
-      break;
-    }
-  }
-  const long tall = (long)((chunks_of(nx, c.vec) + 61) / 62) * ((ny + 13) / 14);
-  c.rows = tall < 8L * cus ? 6 : 14;
-  // A grid of up to 512 x 512 nodes is bound by the latency of a strip's walk
-  // down its rows, not by bandwidth: one column per lane gives the most wavefronts
-  // for the same short walk (measured on cavities of side 128 to 512: 1 column per
-  // lane and 6 rows fastest, or within 5 % of the gather kernel).
-  if ((long)nx * ny <= 512L * 512 && c.rows == 6 && find_kernel(prec, haswall, wall, KIND_STRIP, 1, 6, 1, false))
-    c.vec = 1;
   return c;
 }
 
@@ -392,6 +396,7 @@ lbt1_status bind_config(lbt1_grid *g, const lbt1_kernel_config &want, int cus) {
     if (!k) return fail(LBT1_EINVAL, "no built population kernel at this precision");
     g->kern = g->kern1 = k;
     g->kern2 = nullptr;
+    g->launch_steps = 1;
     g->cfg = lbt1_kernel_config{};
     g->cfg.kernel = LBT1_KERNEL_GATHER;
     g->cfg.fuse = 1;
@@ -414,7 +419,8 @@ lbt1_status bind_config(lbt1_grid *g, const lbt1_kernel_config &want, int cus) {
     // everything bind_config checks) yields to the heuristic rather than failing
     if (have && bind_config(g, tuned, cus) == LBT1_OK) return LBT1_OK;
     if (have) clear_error();
-    c = heuristic_config(g->prec, g->haswall, g->wall, g->nx, g->ny, cus, g->mp, g->periodic & 1u);
+    c = g->mp ? sc_choice(g->prec, g->haswall, g->nx, g->ny, cus)
+              : default_config(g->prec, g->haswall, g->wall, g->nx, g->ny, g->periodic, cus);
   }
   const StepKernel *k = nullptr, *k1 = nullptr, *k2 = nullptr;
   if (c.kernel == LBT1_KERNEL_GATHER) {
@@ -422,7 +428,7 @@ lbt1_status bind_config(lbt1_grid *g, const lbt1_kernel_config &want, int cus) {
     k2 = nullptr;
     c.vec = c.rows = c.waves = 0;
     c.fuse = 1;
-  } else if (c.kernel == LBT1_KERNEL_STRIP) {
+  } else if (c.kernel == LBT1_KERNEL_STRIP && !is_tile(c)) {
     if (!strip_fits(g->nx, c.vec, g->periodic & 1u))
       return fail(LBT1_EINVAL, "strip kernel: vec %d does not divide nx %d on a grid periodic in x", c.vec, g->nx);
     if ((long)chunks_of(g->nx, c.vec) * c.vec > g->L.pitch)
@@ -443,6 +449,14 @@ lbt1_status bind_config(lbt1_grid *g, const lbt1_kernel_config &want, int cus) {
     // three steps per launch: remainders of two steps take the two-step kernel of
     // the same strip shape where one is built
     if (c.fuse == 3) k2 = find_kernel(g->prec, g->haswall, g->wall, KIND_STRIP, c.vec, c.rows, 2, g->mp);
+  } else if (is_tile(c)) {
+    if (g->mp) return fail(LBT1_EINVAL, "multiphase grids have no tile kernel");
+    if (c.fuse < 1 || c.fuse > kMaxTileSteps)
+      return fail(LBT1_EINVAL, "tile kernel: fuse %d must be between 1 and %d", c.fuse, kMaxTileSteps);
+    k = k1 = find_tile(g->prec, g->haswall, g->wall, c.vec, c.rows, c.waves);
+    TileMap m;
+    if (k && !tile_map(g->nx, g->ny, g->periodic, c, c.fuse, &m))
+      return fail(LBT1_EINVAL, "tile kernel: a halo of %d steps leaves nothing of a %d x %d region", c.fuse, c.vec, c.rows);
   } else {
     return fail(LBT1_EINVAL, "unknown kernel family %d", c.kernel);
   }
@@ -452,8 +466,10 @@ lbt1_status bind_config(lbt1_grid *g, const lbt1_kernel_config &want, int cus) {
   g->kern1 = k1;
   g->kern2 = k2;
   g->cfg = c;
-  g->cfg.kernel = k->kind == KIND_GATHER ? LBT1_KERNEL_GATHER : LBT1_KERNEL_STRIP;
-  if (k->kind == KIND_GATHER) {
+  g->launch_steps = k->kind == KIND_TILE ? c.fuse : k->steps;
+  if (k->kind == KIND_TILE) {
+    g->block = dim3(k->threads, 1, 1);  // (its grid depends on the steps of a launch)
+  } else if (k->kind == KIND_GATHER) {
     g->block = dim3(64, 4, 1);
     g->grid = dim3((g->nx + 63) / 64, (g->ny + 3) / 4, 1);
   } else {
@@ -540,8 +556,9 @@ BgkArgs bgk_args(const lbt1_grid *g, int src_parity) {
 }
 
 // One launch of kernel k (g->kern, or its single-step companion g->kern1,
-// which has the same launch shape) reading parity src_parity.
-hipError_t launch_step(lbt1_grid *g, const StepKernel *k, int src_parity, hipStream_t s) {
+// which has the same launch shape) reading parity src_parity; a tile kernel takes
+// `steps` steps.
+hipError_t launch_step(lbt1_grid *g, const StepKernel *k, int src_parity, hipStream_t s, int steps = 1) {
   if (k->kind == KIND_BGK) {
     BgkArgs b = bgk_args(g, src_parity);
     void *args[] = {&b};
@@ -557,6 +574,12 @@ hipError_t launch_step(lbt1_grid *g, const StepKernel *k, int src_parity, hipStr
     const bool companion = k == g->kern1 && k != g->kern;
     return hipLaunchKernel(k->fn, companion ? g->grid1 : g->grid, companion ? g->block1 : g->block, args, 0, s);
   }
+  if (k->kind == KIND_TILE) {
+    TileMap t;
+    if (!tile_map(g->nx, g->ny, g->periodic, g->cfg, steps, &t)) return hipErrorInvalidValue;
+    void *args[] = {&a, &t};
+    return hipLaunchKernel(k->fn, dim3((unsigned)tile_blocks(t, g->ny), 1, 1), g->block, args, 0, s);
+  }
   StripMap m = g->map;
   void *args[] = {&a, &m};
   return hipLaunchKernel(k->fn, g->grid, g->block, args, 0, s);
@@ -566,8 +589,8 @@ hipError_t launch_step(lbt1_grid *g, const StepKernel *k, int src_parity, hipStr
 // it advances burst_steps(g) steps and flips the parity once per launch.
 static const int kBurst = 64;
 
-static int burst_launches(const lbt1_grid *g) { return kBurst / g->kern->steps; }
-static int burst_steps(const lbt1_grid *g) { return burst_launches(g) * g->kern->steps; }
+static int burst_launches(const lbt1_grid *g) { return kBurst / g->launch_steps; }
+static int burst_steps(const lbt1_grid *g) { return burst_launches(g) * g->launch_steps; }
 
 static lbt1_status build_burst(lbt1_grid *g, int p) {
   hipGraph_t graph = nullptr;
@@ -578,17 +601,23 @@ static lbt1_status build_burst(lbt1_grid *g, int p) {
   std::vector<StepArgs> argv(launches);
   std::vector<BgkArgs> bargv(g->pop ? launches : 0);
   StripMap m = g->map;
+  TileMap tm{};
+  if (g->kern->kind == KIND_TILE && !tile_map(g->nx, g->ny, g->periodic, g->cfg, g->launch_steps, &tm)) {
+    hipGraphDestroy(graph);
+    return fail(LBT1_EINVAL, "no tiles");
+  }
   for (int s = 0; s < launches; ++s) {
     argv[s] = step_args(g, (p + s) & 1);
     if (g->pop) bargv[s] = bgk_args(g, (p + s) & 1);
     void *args_gather[] = {g->pop ? (void *)&bargv[s] : (void *)&argv[s]};
     void *args_strip[] = {&argv[s], &m};
+    void *args_tile[] = {&argv[s], &tm};
     hipKernelNodeParams kp{};
     kp.func = const_cast<void *>(g->kern->fn);
-    kp.gridDim = g->grid;
+    kp.gridDim = g->kern->kind == KIND_TILE ? dim3((unsigned)tile_blocks(tm, g->ny), 1, 1) : g->grid;
     kp.blockDim = g->block;
     kp.sharedMemBytes = 0;
-    kp.kernelParams = g->kern->kind == KIND_STRIP ? args_strip : args_gather;
+    kp.kernelParams = g->kern->kind == KIND_STRIP ? args_strip : g->kern->kind == KIND_TILE ? args_tile : args_gather;
     kp.extra = nullptr;
     hipGraphNode_t node;
     if (g->pop && g->mp) {
@@ -629,7 +658,7 @@ static void drop_bursts(lbt1_grid *g) {
 lbt1_status enqueue_steps(lbt1_grid *g, int64_t n, hipStream_t s, bool use_graph) {
   hipError_t e;
   const int bs = burst_steps(g);
-  if (use_graph && n >= bs) {
+  if (use_graph && n >= kBurst) {
     if (!g->graph_valid) {
       drop_bursts(g);
       g->graph_valid = true;
@@ -646,7 +675,17 @@ lbt1_status enqueue_steps(lbt1_grid *g, int64_t n, hipStream_t s, bool use_graph
       g->parity ^= burst_launches(g) & 1;
     }
   }
-  const int K = g->kern->steps;
+  const int K = g->launch_steps;
+  if (g->kern->kind == KIND_TILE) {
+    while (n > 0) {  // any number of steps up to K in a launch
+      const int k = (int)std::min<int64_t>(n, K);
+      if ((e = launch_step(g, g->kern, g->parity, s, k)) != hipSuccess) return hip_fail(e, "step launch");
+      g->parity ^= 1;
+      g->steps += k;
+      n -= k;
+    }
+    return LBT1_OK;
+  }
   // With a two-step companion the remainder after three-step launches is covered
   // by two-step launches: one for 2 left, two for 1 left when the single-step
   // companion is the (slower) gather kernel and at least 4 steps are asked for.
@@ -1362,7 +1401,27 @@ lbt1_status lbt1_autotune(lbt1_grid *g, int32_t steps, int32_t reps, lbt1_kernel
           c.fuse = f;
           cands.push_back(c);
         }
-  // a whole number of fused launches for every candidate
+  if (!g->mp) {
+    int nk = 0;
+    const StepKernel *tk = step_kernels(&nk);
+    for (int i = 0; i < nk; ++i) {
+      if (tk[i].kind != KIND_TILE || tk[i].prec != g->prec || (tk[i].haswall != 0) != g->haswall ||
+          (g->haswall && tk[i].wall != g->wall))
+        continue;
+      for (int f : kTileSteps) {
+        TileMap m;
+        lbt1_kernel_config c{};
+        c.kernel = LBT1_KERNEL_STRIP;
+        c.vec = tk[i].vec;
+        c.rows = tk[i].rows;
+        c.waves = tk[i].threads / 64;
+        c.fuse = f;
+        if (tile_map(g->nx, g->ny, g->periodic, c, f, &m)) cands.push_back(c);
+      }
+    }
+  }
+  // a whole number of fused launches for every strip candidate; the tile kernels take
+  // whole launches of their own, about as many steps
   steps = (steps + 5) / 6 * 6;
   lbt1_status st = LBT1_OK;
   auto time_steps = [&](const int n, const bool use_graph) -> double {
@@ -1379,8 +1438,9 @@ lbt1_status lbt1_autotune(lbt1_grid *g, int32_t steps, int32_t reps, lbt1_kernel
   for (const auto &c : cands) {
     if (bind_config(&t, c, g->cus) != LBT1_OK) continue;
     double cbest = 1e300;
+    const int whole = is_tile(t.cfg) ? std::max(steps / t.launch_steps, 1) * t.launch_steps : steps;
     for (int r = 0; r < reps + 1 && st == LBT1_OK; ++r) {
-      const double ms = time_steps(steps, false);
+      const double ms = time_steps(whole, false);
       if (r > 0) cbest = std::min(cbest, ms);
     }
     if (st) break;
@@ -1406,9 +1466,10 @@ lbt1_status lbt1_autotune(lbt1_grid *g, int32_t steps, int32_t reps, lbt1_kernel
       for (int r = 0; r < std::max(reps, 3) && !st; ++r)
         for (size_t i = 0; i < nf && !st; ++i) {
           if (bind_config(&t, timed[i].second, g->cus) != LBT1_OK) continue;
-          (void)time_steps(3 * kBurst, true);
+          const int n = is_tile(t.cfg) ? 3 * burst_steps(&t) : 3 * kBurst;
+          (void)time_steps(n, true);
           if (st) break;
-          const double ms = time_steps(3 * kBurst, true);
+          const double ms = time_steps(n, true);
           fbest[i] = std::min(fbest[i], ms);
         }
       if (!st) {

@@ -81,6 +81,7 @@ struct lbt1_grid {
   const lbt1::StepKernel *kern1 = nullptr;  // single-step kernel of the same launch shape
   const lbt1::StepKernel *kern2 = nullptr;  // two-step kernel of the same strip shape, when kern takes three
   lbt1::StripMap map{};
+  int launch_steps = 1;  // steps one launch of kern takes
   dim3 grid{1, 1, 1}, block{1, 1, 1};
   dim3 grid1{1, 1, 1}, block1{1, 1, 1};  // launch shape of kern1
   hipGraphExec_t burst[2] = {nullptr, nullptr};

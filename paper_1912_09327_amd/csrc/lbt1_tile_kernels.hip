@@ -1,0 +1,58 @@
+// The tile kernels (several steps per launch on small grids) of one storage precision.
+// Compiled once per precision (LBT1_PREC).
+#include "lbt1_internal.hpp"
+#include "lbt1_tile.hpp"
+
+#ifndef LBT1_PREC
+#error "compile with -DLBT1_PREC=0..3 (P_F64 ... P_BF16S)"
+#endif
+
+namespace lbt1 {
+
+#define LBT1_STR2(x) #x
+#define LBT1_STR(x) LBT1_STR2(x)
+
+#define TILE(P, HW, WL, W, CPL, RPT, TH, ...)                                                        \
+  {P, HW, WL, KIND_TILE, W * CPL, TH / W * RPT, (const void *)&k_step_tile<P, HW, WL, W, CPL, RPT, TH>, \
+   "k_step_tile<" LBT1_STR(P) "," #HW "," #WL "," #W "," #CPL "," #RPT "," #TH ">", 1, 0, TH, __VA_ARGS__}
+#define TILE_WALLED(...) TILE_WALLED_(__VA_ARGS__)
+#define TILE_WALLED_(P, W, CPL, RPT, TH, ...) \
+  TILE(P, true, 0, W, CPL, RPT, TH, __VA_ARGS__), TILE(P, true, 1, W, CPL, RPT, TH, __VA_ARGS__)
+#define TILE_FREE(P, W, CPL, RPT, TH, ...) TILE(P, false, 0, W, CPL, RPT, TH, __VA_ARGS__)
+
+// Two blocks of every shape fit a CU (with one, loads and stores are not overlapped with
+// another block's steps: 128 x 128 regions on 1024 threads take 18 % longer at 4096^2
+// FP32 than 128 x 64 on 512).  Small regions for grids bound by latency, large ones
+// for less halo; with walls the masks take registers, so the largest are smaller.
+// The three figures are the times the runtime's choice is made by, fitted to grids of
+// 48^2 to 8192^2 (see default_config).
+static const StepKernel kTable[] = {
+#if LBT1_PREC == 0
+    TILE_FREE(P_F64, 32, 1, 2, 512, 3.7, 0.442, 0.73), TILE_WALLED(P_F64, 32, 1, 2, 512, 6.6, 0.569, 0.37),
+    TILE_FREE(P_F64, 64, 1, 4, 512, 3.5, 0.972, 0.83), TILE_WALLED(P_F64, 64, 1, 4, 512, 7.8, 1.261, 0.0),
+    TILE_FREE(P_F64, 64, 1, 8, 512, 3.2, 2.056, 1.51),
+#elif LBT1_PREC == 1
+    TILE_FREE(P_F32, 32, 1, 1, 1024, 3.1, 0.235, 0.69), TILE_WALLED(P_F32, 32, 1, 1, 1024, 4.5, 0.350, 0.67),
+    TILE_FREE(P_F32, 64, 1, 2, 1024, 3.2, 0.528, 0.48), TILE_WALLED(P_F32, 64, 1, 2, 1024, 5.6, 0.655, 0.19),
+    TILE_FREE(P_F32, 64, 1, 4, 1024, 3.3, 1.100, 1.20), TILE_WALLED(P_F32, 64, 1, 8, 512, 14.0, 1.200, 1.10),
+    TILE_FREE(P_F32, 64, 2, 8, 512, 6.5, 1.930, 3.00),
+#else
+#if LBT1_PREC == 2
+#define P_HALF P_F16S
+#else
+#define P_HALF P_BF16S
+#endif
+    TILE_FREE(P_HALF, 32, 1, 1, 1024, 3.3, 0.311, 0.41), TILE_WALLED(P_HALF, 32, 1, 1, 1024, 4.6, 0.360, 0.57),
+    TILE_FREE(P_HALF, 64, 1, 2, 1024, 3.3, 0.579, 0.36), TILE_WALLED(P_HALF, 64, 1, 2, 1024, 5.5, 0.681, 0.15),
+    TILE_FREE(P_HALF, 64, 1, 4, 1024, 3.6, 1.368, 0.0), TILE_WALLED(P_HALF, 64, 1, 8, 512, 14.0, 1.400, 0.90),
+    TILE_FREE(P_HALF, 64, 2, 8, 512, 5.9, 2.733, 0.0),
+#endif
+};
+
+template <>
+const StepKernel *tile_kernels<LBT1_PREC>(int *count) {
+  *count = (int)(sizeof(kTable) / sizeof(kTable[0]));
+  return kTable;
+}
+
+}  // namespace lbt1

@@ -96,8 +96,8 @@ enum {
                              format (scale[0] applies), (2 Q) c bytes per node against
                              LBMTau1's 2 N_f c (section 4).  Same flags, walls, lid and
                              force rules; the equilibrium velocity is (j + tau F) / rho.
-                             lbt1_step runs one kernel (set_kernel/autotune: EINVAL); the
-                             grid cannot join a batch */
+                             lbt1_step picks its kernel itself (set_kernel/autotune:
+                             EINVAL); the grid cannot join a batch */
   LBT1_OPT_MULTIPHASE = 8u  /* single-component multiphase flow: the Shan-Chen interaction
                              force of the paper's Eq. f_sc, F(x) = -G psi(x) sum_k w_k
                              psi(x + e_k) e_k with psi(rho) = rho0 (1 - exp(-rho / rho0))

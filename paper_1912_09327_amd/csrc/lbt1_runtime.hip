@@ -243,13 +243,13 @@ lbt1_status check_device(int *dev_out, int *cus) {
 static bool strip_fits(int nx, int vec, bool periodic_x) { return vec >= 1 && (nx % vec == 0 || !periodic_x); }
 static int chunks_of(int nx, int vec) { return (nx + vec - 1) / vec; }
 
-// The tile kernel with regions of w columns and `rows` rows on `waves` wavefronts.
-static const StepKernel *find_tile(int prec, bool haswall, int wall, int w, int rows, int waves) {
+// The tile kernel of a kind with regions of w columns and `rows` rows on `waves` wavefronts.
+static const StepKernel *find_tile(int kind, int prec, bool haswall, int wall, int w, int rows, int waves) {
   int n = 0;
   const StepKernel *t = step_kernels(&n);
   for (int i = 0; i < n; ++i) {
     const StepKernel &k = t[i];
-    if (k.kind == KIND_TILE && k.prec == prec && (k.haswall != 0) == haswall && (!haswall || k.wall == wall) &&
+    if (k.kind == kind && k.prec == prec && (k.haswall != 0) == haswall && (!haswall || k.wall == wall) &&
         k.vec == w && k.rows == rows && k.threads == 64 * waves)
       return &k;
   }
@@ -299,19 +299,55 @@ static bool tile_map(int nx, int ny, uint32_t periodic, const lbt1_kernel_config
   m->oy = c.rows - 2 * m->hy;
   if (m->ox < 1 || m->oy < 1) return false;
   m->tiles_x = (nx + m->ox - 1) / m->ox;
+  m->tiles = m->tiles_x * ((ny + m->oy - 1) / m->oy);
+  m->per_xcd = (m->tiles + 7) / 8;
   return true;
 }
-static long tile_blocks(const TileMap &m, int ny) { return (long)m.tiles_x * ((ny + m.oy - 1) / m.oy); }
+static bool is_tile_kind(const StepKernel *k) { return k->kind == KIND_TILE || k->kind == KIND_BGK_TILE; }
+static dim3 tile_grid(const TileMap &m) { return dim3(8 * (unsigned)m.per_xcd, 1, 1); }
 
 // Steps of a launch the choice is made over (and the autotuner's candidates).  One step
 // of a launch widens the halo by a node; three and fewer measured slower on every grid.
 static const int kTileSteps[] = {4, 6, 8, 10, 12, 16, kMaxTileSteps};
 
-// Default without a tuned entry: the tile kernel and steps per launch with the least
-// modelled time per step.  A launch takes us_launch and, for each block that falls to
+// The tile kernel of a kind and the steps per launch with the least modelled time per
+// step, which goes to *us_out.  A launch takes us_launch and, for each block that falls to
 // the busiest CU (past eight rounds the average: blocks end at different times), us_step
 // per step and us_block.  On 80 grids of 48^2 to 8192^2, periodic and cavities, FP64,
 // FP32 and FP16S, what it picks is within 2 % of the fastest shape on average.
+static lbt1_kernel_config tile_choice(int kind, int prec, bool haswall, int wall, int nx, int ny, uint32_t periodic, int cus,
+                                      double *us_out) {
+  lbt1_kernel_config best{};
+  best.kernel = LBT1_KERNEL_GATHER;
+  double best_us = 1e300;
+  int n = 0;
+  const StepKernel *t = step_kernels(&n);
+  for (int i = 0; i < n; ++i) {
+    const StepKernel &k = t[i];
+    if (k.kind != kind || k.prec != prec || (k.haswall != 0) != haswall || (haswall && k.wall != wall)) continue;
+    for (int steps : kTileSteps) {
+      lbt1_kernel_config c{};
+      c.kernel = LBT1_KERNEL_STRIP;
+      c.vec = k.vec;
+      c.rows = k.rows;
+      c.waves = k.threads / 64;
+      c.fuse = steps;
+      TileMap m;
+      if (!tile_map(nx, ny, periodic, c, steps, &m)) continue;
+      const double per_cu = (double)m.tiles / cus;
+      const double rounds = per_cu <= 8 ? std::ceil(per_cu) : per_cu + 0.5;
+      const double us = (k.us_launch + rounds * (steps * k.us_step + k.us_block)) / steps;
+      if (us < best_us) {
+        best_us = us;
+        best = c;
+      }
+    }
+  }
+  *us_out = best_us;
+  return best;
+}
+
+// Default without a tuned entry: the tile kernel tile_choice finds.
 //
 // In FP32 and FP64 that beat every strip and gather kernel at each size (us per step,
 // tile against the best of those: FP32 periodic 256^2 0.77 / 3.4, 1024^2 3.1 / 7.1,
@@ -323,32 +359,8 @@ static const int kTileSteps[] = {4, 6, 8, 10, 12, 16, kMaxTileSteps};
 // but 2048^2 9.75 against 9.2 and 14.1 against 11.1), by a time of `half_strip` us per
 // million nodes and `half_base` us, fitted to the same grids.
 static lbt1_kernel_config default_config(int prec, bool haswall, int wall, int nx, int ny, uint32_t periodic, int cus) {
-  lbt1_kernel_config best{};
-  best.kernel = LBT1_KERNEL_GATHER;
-  double best_us = 1e300;
-  int n = 0;
-  const StepKernel *t = step_kernels(&n);
-  for (int i = 0; i < n; ++i) {
-    const StepKernel &k = t[i];
-    if (k.kind != KIND_TILE || k.prec != prec || (k.haswall != 0) != haswall || (haswall && k.wall != wall)) continue;
-    for (int steps : kTileSteps) {
-      lbt1_kernel_config c{};
-      c.kernel = LBT1_KERNEL_STRIP;
-      c.vec = k.vec;
-      c.rows = k.rows;
-      c.waves = k.threads / 64;
-      c.fuse = steps;
-      TileMap m;
-      if (!tile_map(nx, ny, periodic, c, steps, &m)) continue;
-      const double per_cu = (double)tile_blocks(m, ny) / cus;
-      const double rounds = per_cu <= 8 ? std::ceil(per_cu) : per_cu + 0.5;
-      const double us = (k.us_launch + rounds * (steps * k.us_step + k.us_block)) / steps;
-      if (us < best_us) {
-        best_us = us;
-        best = c;
-      }
-    }
-  }
+  double best_us;
+  lbt1_kernel_config best = tile_choice(KIND_TILE, prec, haswall, wall, nx, ny, periodic, cus, &best_us);
   const double half_strip = haswall ? 1.70 : 1.62, half_base = haswall ? 5.0 : 2.5;
   if ((prec == LBT1_F16S || prec == LBT1_BF16S) && strip_fits(nx, 2, periodic & 1u) &&
       half_strip * 1e-6 * nx * ny + half_base < best_us && find_kernel(prec, haswall, wall, KIND_STRIP, 2, 14, 2, false)) {
@@ -391,11 +403,23 @@ static lbt1_kernel_config sc_choice(int prec, bool haswall, int nx, int ny, int 
 // Resolve a configuration into a kernel and launch shape for grid g.
 lbt1_status bind_config(lbt1_grid *g, const lbt1_kernel_config &want, int cus) {
   if (g->pop) {
-    // one kernel: a thread per node (the gather launch shape)
+    g->kern2 = nullptr;
+    g->graph_valid = false;
+    if (!g->mp) {
+      double us;
+      g->cfg = tile_choice(KIND_BGK_TILE, g->prec, g->haswall, g->wall, g->nx, g->ny, g->periodic, cus, &us);
+      const StepKernel *k =
+          find_tile(KIND_BGK_TILE, g->prec, g->haswall, g->wall, g->cfg.vec, g->cfg.rows, g->cfg.waves);
+      if (!k) return fail(LBT1_EINVAL, "no built population kernel at this precision");
+      g->kern = g->kern1 = k;
+      g->launch_steps = g->cfg.fuse;
+      g->block = g->block1 = dim3(k->threads, 1, 1);
+      return LBT1_OK;
+    }
+    // multiphase: one step at a time, a thread per node (the gather launch shape)
     const StepKernel *k = find_kernel(g->prec, g->haswall, g->wall, KIND_BGK, 0, 0, 1, g->mp);
     if (!k) return fail(LBT1_EINVAL, "no built population kernel at this precision");
     g->kern = g->kern1 = k;
-    g->kern2 = nullptr;
     g->launch_steps = 1;
     g->cfg = lbt1_kernel_config{};
     g->cfg.kernel = LBT1_KERNEL_GATHER;
@@ -403,7 +427,6 @@ lbt1_status bind_config(lbt1_grid *g, const lbt1_kernel_config &want, int cus) {
     const int tiles = ((g->nx + 63) / 64) * ((g->ny + 3) / 4);
     g->block = g->block1 = dim3(256, 1, 1);
     g->grid = g->grid1 = dim3((tiles + 7) / 8 * 8, 1, 1);
-    g->graph_valid = false;
     return LBT1_OK;
   }
   lbt1_kernel_config c = want;
@@ -453,7 +476,7 @@ lbt1_status bind_config(lbt1_grid *g, const lbt1_kernel_config &want, int cus) {
     if (g->mp) return fail(LBT1_EINVAL, "multiphase grids have no tile kernel");
     if (c.fuse < 1 || c.fuse > kMaxTileSteps)
       return fail(LBT1_EINVAL, "tile kernel: fuse %d must be between 1 and %d", c.fuse, kMaxTileSteps);
-    k = k1 = find_tile(g->prec, g->haswall, g->wall, c.vec, c.rows, c.waves);
+    k = k1 = find_tile(KIND_TILE, g->prec, g->haswall, g->wall, c.vec, c.rows, c.waves);
     TileMap m;
     if (k && !tile_map(g->nx, g->ny, g->periodic, c, c.fuse, &m))
       return fail(LBT1_EINVAL, "tile kernel: a halo of %d steps leaves nothing of a %d x %d region", c.fuse, c.vec, c.rows);
@@ -562,23 +585,27 @@ hipError_t launch_step(lbt1_grid *g, const StepKernel *k, int src_parity, hipStr
   if (k->kind == KIND_BGK) {
     BgkArgs b = bgk_args(g, src_parity);
     void *args[] = {&b};
-    if (g->mp) {
-      hipError_t e = hipLaunchKernel(bgk_psi_kernel(g->prec), g->grid, g->block, args, 0, s);
-      if (e != hipSuccess) return e;
-    }
+    hipError_t e = hipLaunchKernel(bgk_psi_kernel(g->prec), g->grid, g->block, args, 0, s);
+    if (e != hipSuccess) return e;
     return hipLaunchKernel(k->fn, g->grid, g->block, args, 0, s);
+  }
+  if (is_tile_kind(k)) {
+    TileMap t;
+    if (!tile_map(g->nx, g->ny, g->periodic, g->cfg, steps, &t)) return hipErrorInvalidValue;
+    StepArgs a{};
+    BgkArgs b{};
+    if (g->pop)
+      b = bgk_args(g, src_parity);
+    else
+      a = step_args(g, src_parity);
+    void *args[] = {g->pop ? (void *)&b : (void *)&a, &t};
+    return hipLaunchKernel(k->fn, tile_grid(t), g->block, args, 0, s);
   }
   StepArgs a = step_args(g, src_parity);
   if (k->kind == KIND_GATHER) {
     void *args[] = {&a};
     const bool companion = k == g->kern1 && k != g->kern;
     return hipLaunchKernel(k->fn, companion ? g->grid1 : g->grid, companion ? g->block1 : g->block, args, 0, s);
-  }
-  if (k->kind == KIND_TILE) {
-    TileMap t;
-    if (!tile_map(g->nx, g->ny, g->periodic, g->cfg, steps, &t)) return hipErrorInvalidValue;
-    void *args[] = {&a, &t};
-    return hipLaunchKernel(k->fn, dim3((unsigned)tile_blocks(t, g->ny), 1, 1), g->block, args, 0, s);
   }
   StripMap m = g->map;
   void *args[] = {&a, &m};
@@ -602,7 +629,7 @@ static lbt1_status build_burst(lbt1_grid *g, int p) {
   std::vector<BgkArgs> bargv(g->pop ? launches : 0);
   StripMap m = g->map;
   TileMap tm{};
-  if (g->kern->kind == KIND_TILE && !tile_map(g->nx, g->ny, g->periodic, g->cfg, g->launch_steps, &tm)) {
+  if (is_tile_kind(g->kern) && !tile_map(g->nx, g->ny, g->periodic, g->cfg, g->launch_steps, &tm)) {
     hipGraphDestroy(graph);
     return fail(LBT1_EINVAL, "no tiles");
   }
@@ -611,13 +638,13 @@ static lbt1_status build_burst(lbt1_grid *g, int p) {
     if (g->pop) bargv[s] = bgk_args(g, (p + s) & 1);
     void *args_gather[] = {g->pop ? (void *)&bargv[s] : (void *)&argv[s]};
     void *args_strip[] = {&argv[s], &m};
-    void *args_tile[] = {&argv[s], &tm};
+    void *args_tile[] = {args_gather[0], &tm};
     hipKernelNodeParams kp{};
     kp.func = const_cast<void *>(g->kern->fn);
-    kp.gridDim = g->kern->kind == KIND_TILE ? dim3((unsigned)tile_blocks(tm, g->ny), 1, 1) : g->grid;
+    kp.gridDim = is_tile_kind(g->kern) ? tile_grid(tm) : g->grid;
     kp.blockDim = g->block;
     kp.sharedMemBytes = 0;
-    kp.kernelParams = g->kern->kind == KIND_STRIP ? args_strip : g->kern->kind == KIND_TILE ? args_tile : args_gather;
+    kp.kernelParams = g->kern->kind == KIND_STRIP ? args_strip : is_tile_kind(g->kern) ? args_tile : args_gather;
     kp.extra = nullptr;
     hipGraphNode_t node;
     if (g->pop && g->mp) {
@@ -676,7 +703,7 @@ lbt1_status enqueue_steps(lbt1_grid *g, int64_t n, hipStream_t s, bool use_graph
     }
   }
   const int K = g->launch_steps;
-  if (g->kern->kind == KIND_TILE) {
+  if (is_tile_kind(g->kern)) {
     while (n > 0) {  // any number of steps up to K in a launch
       const int k = (int)std::min<int64_t>(n, K);
       if ((e = launch_step(g, g->kern, g->parity, s, k)) != hipSuccess) return hip_fail(e, "step launch");

@@ -40,6 +40,100 @@ struct TileShared {
   C v[kCopies][6][NODES];
 };
 
+// all ones where bit b of w is set, else 0, and the choice between two values by such a
+// mask: two vector operations for a select, and no condition held in scalar registers
+__device__ __forceinline__ uint32_t spread(const uint32_t w, const int b) {
+  return (uint32_t)((int32_t)(w << (31 - b)) >> 31);
+}
+__device__ __forceinline__ float pick(const uint32_t m, const float yes, const float no) {
+  return __uint_as_float((__float_as_uint(yes) & m) | (__float_as_uint(no) & ~m));
+}
+__device__ __forceinline__ double pick(const uint32_t m, const double yes, const double no) {
+  const uint64_t a = (uint64_t)__double_as_longlong(yes), b = (uint64_t)__double_as_longlong(no);
+  const uint32_t lo = ((uint32_t)a & m) | ((uint32_t)b & ~m), hi = ((uint32_t)(a >> 32) & m) | ((uint32_t)(b >> 32) & ~m);
+  return __longlong_as_double((long long)((uint64_t)hi << 32 | lo));
+}
+
+// Lattice column and row of every node of a thread at (x, y0), -1 outside a non-periodic
+// axis (one division per axis: the following ones step and wrap).
+template <int CPL, int RPT>
+struct TilePlace {
+  int wx[CPL], wy[RPT];
+  __device__ __forceinline__ TilePlace(const int x, const int y0, const int nx, const int ny, const bool px,
+                                       const bool py) {
+    wx[0] = wrap_axis(x, nx, px);
+#pragma unroll
+    for (int c = 1; c < CPL; ++c) {
+      const int n = wx[c - 1] + 1;
+      wx[c] = px ? (n == nx ? 0 : n) : (x + c >= 0 && x + c < nx ? x + c : -1);
+    }
+    wy[0] = wrap_axis(y0, ny, py);
+#pragma unroll
+    for (int i = 1; i < RPT; ++i) {
+      const int n = wy[i - 1] + 1;
+      wy[i] = py ? (n == ny ? 0 : n) : (y0 + i >= 0 && y0 + i < ny ? y0 + i : -1);
+    }
+  }
+};
+
+// Flags of a thread's nodes: a FLUID bit per node (node i * CPL + c), and per row of the
+// thread (solid[1 + i]) a SOLID bit per column (bit c + 1).  Outside the grid SOLID.
+template <int CPL, int RPT>
+__device__ __forceinline__ void tile_flags(const uint8_t *flags, const int pitch, const TilePlace<CPL, RPT> &at,
+                                           uint32_t (&solid)[RPT + 2], uint32_t &fluid) {
+  fluid = 0;
+#pragma unroll
+  for (int i = 0; i < RPT; ++i) {
+    uint32_t sb = 0;
+#pragma unroll
+    for (int c = 0; c < CPL; ++c) {
+      const bool in = at.wy[i] >= 0 && at.wx[c] >= 0;
+      const uint8_t f = flags[(long)max(at.wy[i], 0) * pitch + max(at.wx[c], 0)];
+      sb |= (uint32_t)(!in || f == NODE_SOLID) << (c + 1);
+      fluid |= (uint32_t)(in && f == NODE_FLUID) << (i * CPL + c);
+    }
+    solid[i + 1] = sb;
+  }
+}
+
+// Eight bits per node, bit q - 1 set where its source along e_q is a wall, from the SOLID
+// bits of the thread and of the threads next to it (through `bits`, 2 * THREADS words of
+// LDS); outside the region SOLID (a grid edge, or the halo).
+template <int W, int CPL, int RPT, int THREADS>
+__device__ __forceinline__ void tile_walls(uint32_t (&solid)[RPT + 2], uint32_t *bits,
+                                           uint32_t (&from_wall)[(RPT * CPL + 3) / 4]) {
+  const int lane = threadIdx.x & (W - 1), grp = threadIdx.x / W;
+#pragma unroll
+  for (int i = 1; i <= RPT; ++i) {
+    const uint32_t lw = (uint32_t)dpp_shift<kDppWaveShr1>((int)(solid[i] >> CPL & 1u));
+    const uint32_t rw = (uint32_t)dpp_shift<kDppWaveShl1>((int)(solid[i] >> 1 & 1u));
+    solid[i] |= (lane == 0 ? 1u : lw) | (lane == W - 1 ? 1u : rw) << (CPL + 1);
+  }
+  bits[threadIdx.x] = solid[1];
+  bits[THREADS + threadIdx.x] = solid[RPT];
+  __syncthreads();
+  solid[0] = grp > 0 ? bits[THREADS + threadIdx.x - W] : 0xffffffffu;
+  solid[RPT + 1] = grp < THREADS / W - 1 ? bits[threadIdx.x + W] : 0xffffffffu;
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < (RPT * CPL + 3) / 4; ++k) from_wall[k] = 0;
+#pragma unroll
+  for (int i = 0; i < RPT; ++i)
+#pragma unroll
+    for (int c = 0; c < CPL; ++c)
+#pragma unroll
+      for (int q = 1; q < 9; ++q) {
+        const int node = i * CPL + c;
+        from_wall[node / 4] |= (solid[i + 1 - kEy[q]] >> (c + 1 - kEx[q]) & 1u) << (node % 4 * 8 + q - 1);
+      }
+}
+
+// The tile of a block: block b runs on XCD b % 8, and each XCD takes a contiguous range of
+// tiles along the rows, so the halos that neighbouring tiles share meet in one L2.
+__device__ __forceinline__ int tile_of(const TileMap &m) {
+  return (int)(blockIdx.x & 7) * m.per_xcd + (int)(blockIdx.x >> 3);
+}
+
 template <int P, int WALL, int W, int CPL, int RPT, int THREADS, bool UNIT>
 struct TileRegion {
   using T = Traits<P>;
@@ -164,20 +258,6 @@ struct TileRegion {
       }
       if (Shared::kCopies == 1) __syncthreads();
     }
-  }
-
-  // all ones where bit b of w is set, else 0, and the choice between two values by such a
-  // mask: two vector operations for a select, and no condition held in scalar registers
-  static __device__ __forceinline__ uint32_t spread(const uint32_t w, const int b) {
-    return (uint32_t)((int32_t)(w << (31 - b)) >> 31);
-  }
-  static __device__ __forceinline__ float pick(const uint32_t m, const float yes, const float no) {
-    return __uint_as_float((__float_as_uint(yes) & m) | (__float_as_uint(no) & ~m));
-  }
-  static __device__ __forceinline__ double pick(const uint32_t m, const double yes, const double no) {
-    const uint64_t a = (uint64_t)__double_as_longlong(yes), b = (uint64_t)__double_as_longlong(no);
-    const uint32_t lo = ((uint32_t)a & m) | ((uint32_t)b & ~m), hi = ((uint32_t)(a >> 32) & m) | ((uint32_t)(b >> 32) & ~m);
-    return __longlong_as_double((long long)((uint64_t)hi << 32 | lo));
   }
 
   // The same walk with walls.  from_wall: eight bits per node, bit q - 1 set where its
@@ -314,7 +394,7 @@ struct TileRegion {
 
 template <int P, bool HASWALL, int WALL, int W, int CPL, int RPT, int THREADS, bool UNIT>
 __device__ __forceinline__ void tile_body(
-    const StepArgs &a, const TileMap &m, typename TileRegion<P, WALL, W, CPL, RPT, THREADS, UNIT>::Shared &sh) {
+    const StepArgs &a, const TileMap &m, const int tile, typename TileRegion<P, WALL, W, CPL, RPT, THREADS, UNIT>::Shared &sh) {
   using R = TileRegion<P, WALL, W, CPL, RPT, THREADS, UNIT>;
   using T = Traits<P>;
   using C = typename T::C;
@@ -335,35 +415,21 @@ __device__ __forceinline__ void tile_body(
   // the outermost groups read their own rows instead of a neighbour's: halo or grid edge
   r.above = grp > 0 ? r.at - W * CPL : r.at;
   r.below = grp < R::GROUPS - 1 ? r.at + W * CPL : r.at;
-  const int ty = blockIdx.x / m.tiles_x, tx = blockIdx.x - ty * m.tiles_x;
+  const int ty = tile / m.tiles_x, tx = tile - ty * m.tiles_x;
   const int x = tx * m.ox - m.hx + col;
   const int y0 = ty * m.oy - m.hy + grp * RPT;
   const bool px = !HASWALL || (a.periodic & 1u), py = !HASWALL || (a.periodic & 2u);
   const S *const s0 = static_cast<const S *>(a.src[0]), *const s1 = static_cast<const S *>(a.src[1]),
                 *const s2 = static_cast<const S *>(a.src[2]);
 
-  // lattice column and row of every node of this thread, -1 outside a non-periodic axis
-  // (one division per axis: the following ones step and wrap)
-  int wx[CPL], wy[RPT];
-  wx[0] = wrap_axis(x, a.nx, px);
-#pragma unroll
-  for (int c = 1; c < CPL; ++c) {
-    const int n = wx[c - 1] + 1;
-    wx[c] = px ? (n == a.nx ? 0 : n) : (x + c >= 0 && x + c < a.nx ? x + c : -1);
-  }
-  wy[0] = wrap_axis(y0, a.ny, py);
-#pragma unroll
-  for (int i = 1; i < RPT; ++i) {
-    const int n = wy[i - 1] + 1;
-    wy[i] = py ? (n == a.ny ? 0 : n) : (y0 + i >= 0 && y0 + i < a.ny ? y0 + i : -1);
-  }
+  const TilePlace<CPL, RPT> at(x, y0, a.nx, a.ny, px, py);
   // x is a multiple of CPL, so where CPL divides nx or x is not periodic (the rest of a
   // row's last chunk is padding) a chunk is one aligned vector
   SP v0[RPT], v1[RPT], v2[RPT];
   if (CPL > 1 && !(px && a.nx % CPL != 0)) {
 #pragma unroll
     for (int i = 0; i < RPT; ++i) {
-      const long k = (long)max(wy[i], 0) * a.rs + max(wx[0], 0);
+      const long k = (long)max(at.wy[i], 0) * a.rs + max(at.wx[0], 0);
       v0[i] = *reinterpret_cast<const SP *>(s0 + k);
       v1[i] = *reinterpret_cast<const SP *>(s1 + k);
       v2[i] = *reinterpret_cast<const SP *>(s2 + k);
@@ -373,7 +439,7 @@ __device__ __forceinline__ void tile_body(
     for (int i = 0; i < RPT; ++i)
 #pragma unroll
       for (int c = 0; c < CPL; ++c) {
-        const long k = (long)max(wy[i], 0) * a.rs + max(wx[c], 0);
+        const long k = (long)max(at.wy[i], 0) * a.rs + max(at.wx[c], 0);
         v0[i].v[c] = s0[k];
         v1[i].v[c] = s1[k];
         v2[i].v[c] = s2[k];
@@ -382,20 +448,7 @@ __device__ __forceinline__ void tile_body(
   uint32_t solid[RPT + 2], fluid = 0;
   (void)solid;
   bool walls = false;
-  if constexpr (HASWALL) {
-#pragma unroll
-    for (int i = 0; i < RPT; ++i) {
-      uint32_t sb = 0;
-#pragma unroll
-      for (int c = 0; c < CPL; ++c) {
-        const bool in = wy[i] >= 0 && wx[c] >= 0;
-        const uint8_t f = a.flags[(long)max(wy[i], 0) * a.pitch + max(wx[c], 0)];
-        sb |= (uint32_t)(!in || f == NODE_SOLID) << (c + 1);
-        fluid |= (uint32_t)(in && f == NODE_FLUID) << (i * CPL + c);
-      }
-      solid[i + 1] = sb;
-    }
-  }
+  if constexpr (HASWALL) tile_flags<CPL, RPT>(a.flags, a.pitch, at, solid, fluid);
 #pragma unroll
   for (int i = 0; i < RPT; ++i)
 #pragma unroll
@@ -416,31 +469,8 @@ __device__ __forceinline__ void tile_body(
   }
   if constexpr (HASWALL) {
     if (walls) {
-      // SOLID bits of the columns and rows next to this thread's; outside the region SOLID
-      // (a grid edge, or the halo)
-#pragma unroll
-      for (int i = 1; i <= RPT; ++i) {
-        const uint32_t lw = (uint32_t)dpp_shift<kDppWaveShr1>((int)(solid[i] >> CPL & 1u));
-        const uint32_t rw = (uint32_t)dpp_shift<kDppWaveShl1>((int)(solid[i] >> 1 & 1u));
-        solid[i] |= (lane == 0 ? 1u : lw) | (lane == W - 1 ? 1u : rw) << (CPL + 1);
-      }
-      uint32_t *bits = reinterpret_cast<uint32_t *>(&sh);
-      bits[threadIdx.x] = solid[1];
-      bits[THREADS + threadIdx.x] = solid[RPT];
-      __syncthreads();
-      solid[0] = grp > 0 ? bits[THREADS + threadIdx.x - W] : 0xffffffffu;
-      solid[RPT + 1] = grp < R::GROUPS - 1 ? bits[threadIdx.x + W] : 0xffffffffu;
-      __syncthreads();
-      uint32_t from_wall[R::kWords] = {};
-#pragma unroll
-      for (int i = 0; i < RPT; ++i)
-#pragma unroll
-        for (int c = 0; c < CPL; ++c)
-#pragma unroll
-          for (int q = 1; q < 9; ++q) {
-            const int node = i * CPL + c;
-            from_wall[node / 4] |= (solid[i + 1 - kEy[q]] >> (c + 1 - kEx[q]) & 1u) << (node % 4 * 8 + q - 1);
-          }
+      uint32_t from_wall[R::kWords];
+      tile_walls<W, CPL, RPT, THREADS>(solid, reinterpret_cast<uint32_t *>(&sh), from_wall);
       r.march_walls(sh, m.steps, from_wall, fluid);
     } else {
       r.march(sh, m.steps);
@@ -487,14 +517,16 @@ __device__ __forceinline__ void tile_body(
 template <int P, bool HASWALL, int WALL, int W, int CPL, int RPT, int THREADS>
 __global__ void __launch_bounds__(THREADS) k_step_tile(StepArgs a, TileMap m) {
   __shared__ __align__(16) TileShared<typename Traits<P>::C, THREADS * CPL> sh;
+  const int tile = tile_of(m);
+  if (tile >= m.tiles) return;  // uniform across the block
   if constexpr (Traits<P>::kScaled) {
     // unit storage scales (the default): the codec without its multiplications
     if (a.sc_d == 1.0 && a.sc_j == 1.0 && a.is_d == 1.0 && a.is_j == 1.0)
-      tile_body<P, HASWALL, WALL, W, CPL, RPT, THREADS, true>(a, m, sh);
+      tile_body<P, HASWALL, WALL, W, CPL, RPT, THREADS, true>(a, m, tile, sh);
     else
-      tile_body<P, HASWALL, WALL, W, CPL, RPT, THREADS, false>(a, m, sh);
+      tile_body<P, HASWALL, WALL, W, CPL, RPT, THREADS, false>(a, m, tile, sh);
   } else {
-    tile_body<P, HASWALL, WALL, W, CPL, RPT, THREADS, true>(a, m, sh);
+    tile_body<P, HASWALL, WALL, W, CPL, RPT, THREADS, true>(a, m, tile, sh);
   }
 }
 

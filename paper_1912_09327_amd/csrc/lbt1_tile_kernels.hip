@@ -1,5 +1,6 @@
 // The tile kernels (several steps per launch on small grids) of one storage precision.
 // Compiled once per precision (LBT1_PREC).
+#include "lbt1_bgk_tile.hpp"
 #include "lbt1_internal.hpp"
 #include "lbt1_tile.hpp"
 
@@ -26,16 +27,29 @@ namespace lbt1 {
 // for less halo; with walls the masks take registers, so the largest are smaller.
 // The three figures are the times the runtime's choice is made by, fitted to grids of
 // 48^2 to 8192^2 (see default_config).
+#define BGK_TILE(P, HW, WL, W, RPT, TH, ...)                                                        \
+  {P, HW, WL, KIND_BGK_TILE, W, TH / W * RPT, (const void *)&k_bgk_tile<P, HW, WL, W, RPT, TH>,     \
+   "k_bgk_tile<" LBT1_STR(P) "," #HW "," #WL "," #W "," #RPT "," #TH ">", 1, 0, TH, __VA_ARGS__}
+#define BGK_FREE(P, W, RPT, TH, ...) BGK_TILE(P, false, 0, W, RPT, TH, __VA_ARGS__)
+#define BGK_WALLED(...) BGK_WALLED_(__VA_ARGS__)
+#define BGK_WALLED_(P, W, RPT, TH, ...) \
+  BGK_TILE(P, true, 0, W, RPT, TH, __VA_ARGS__), BGK_TILE(P, true, 1, W, RPT, TH, __VA_ARGS__)
+
 static const StepKernel kTable[] = {
 #if LBT1_PREC == 0
     TILE_FREE(P_F64, 32, 1, 2, 512, 3.7, 0.442, 0.73), TILE_WALLED(P_F64, 32, 1, 2, 512, 6.6, 0.569, 0.37),
     TILE_FREE(P_F64, 64, 1, 4, 512, 3.5, 0.972, 0.83), TILE_WALLED(P_F64, 64, 1, 4, 512, 7.8, 1.261, 0.0),
     TILE_FREE(P_F64, 64, 1, 8, 512, 3.2, 2.056, 1.51),
+    BGK_FREE(P_F64, 32, 2, 512, 4.2, 0.522, 2.95), BGK_WALLED(P_F64, 32, 2, 512, 8.3, 0.679, 1.82),
+    BGK_FREE(P_F64, 64, 4, 512, 3.4, 1.150, 5.33), BGK_WALLED(P_F64, 64, 4, 512, 6.4, 1.588, 6.24),
 #elif LBT1_PREC == 1
     TILE_FREE(P_F32, 32, 1, 1, 1024, 3.1, 0.235, 0.69), TILE_WALLED(P_F32, 32, 1, 1, 1024, 4.5, 0.350, 0.67),
     TILE_FREE(P_F32, 64, 1, 2, 1024, 3.2, 0.528, 0.48), TILE_WALLED(P_F32, 64, 1, 2, 1024, 5.6, 0.655, 0.19),
     TILE_FREE(P_F32, 64, 1, 4, 1024, 3.3, 1.100, 1.20), TILE_WALLED(P_F32, 64, 1, 8, 512, 14.0, 1.200, 1.10),
     TILE_FREE(P_F32, 64, 2, 8, 512, 6.5, 1.930, 3.00),
+    BGK_FREE(P_F32, 32, 2, 512, 4.2, 0.276, 1.92), BGK_WALLED(P_F32, 32, 2, 512, 6.8, 0.356, 1.36),
+    BGK_FREE(P_F32, 64, 4, 512, 4.1, 0.752, 3.20), BGK_WALLED(P_F32, 64, 4, 512, 7.7, 0.953, 1.40),
+    BGK_FREE(P_F32, 64, 8, 512, 2.9, 1.897, 4.96),
 #else
 #if LBT1_PREC == 2
 #define P_HALF P_F16S
@@ -46,6 +60,9 @@ static const StepKernel kTable[] = {
     TILE_FREE(P_HALF, 64, 1, 2, 1024, 3.3, 0.579, 0.36), TILE_WALLED(P_HALF, 64, 1, 2, 1024, 5.5, 0.681, 0.15),
     TILE_FREE(P_HALF, 64, 1, 4, 1024, 3.6, 1.368, 0.0), TILE_WALLED(P_HALF, 64, 1, 8, 512, 14.0, 1.400, 0.90),
     TILE_FREE(P_HALF, 64, 2, 8, 512, 5.9, 2.733, 0.0),
+    BGK_FREE(P_HALF, 32, 2, 512, 4.7, 0.632, 0.72), BGK_WALLED(P_HALF, 32, 2, 512, 7.4, 0.770, 0.00),
+    BGK_FREE(P_HALF, 64, 4, 512, 5.4, 1.333, 0.64), BGK_WALLED(P_HALF, 64, 4, 512, 9.4, 1.512, 0.00),
+    BGK_FREE(P_HALF, 64, 8, 512, 5.4, 2.841, 1.41),
 #endif
 };
 

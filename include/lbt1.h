@@ -412,6 +412,9 @@ enum {
   LBT1_BATCH_FUSE_MIXED = 2   /* the fused class except for grids of the 4-column class narrower
                                  than 1024 columns (the default) */
 };
+/* The default shape (LBT1_BATCH_FUSE_MIXED, lds 0, every height 0, vec_cap 0 or 4) leaves
+ * the classes to the library, which then runs every grid on regions of nodes held in
+ * registers for several steps per launch (lbt1_kernel_config, vec 32 and more). */
 typedef struct {
   int32_t fuse;     /* LBT1_BATCH_FUSE_* */
   int32_t lds;      /* 1: grids that fit run resident in LDS (class 4); 0: they do not */

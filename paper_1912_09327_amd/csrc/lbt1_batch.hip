@@ -36,16 +36,11 @@ namespace lbt1 {
 // Work classes: one step per launch at 1, 2, 4 columns per lane, two steps per
 // launch at 2 columns per lane, and small grids resident in LDS for a whole burst
 // (one launch per burst, two columns per lane).
-enum { CLS_V1 = 0, CLS_V2 = 1, CLS_V4 = 2, CLS_F2 = 3, CLS_LDS = 4, kClasses = 5 };
-static const int kVecOfClass[kClasses] = {1, 2, 4, 2, 2};
-static const int kStepsOfClass[kClasses] = {1, 1, 1, 2, 0};  // 0: every step of the burst in one launch
-
-// launches a class takes for a burst of K steps, and the parity flips of a grid of
-// the class that takes k steps in it
-static int class_launches(int c, int K) { return kStepsOfClass[c] ? (K + kStepsOfClass[c] - 1) / kStepsOfClass[c] : 1; }
-static int class_flips(int c, int k) {
-  return k <= 0 ? 0 : kStepsOfClass[c] ? (k + kStepsOfClass[c] - 1) / kStepsOfClass[c] : 1;
-}
+// And regions of nodes held in registers for several steps per launch, the default.
+enum { CLS_V1 = 0, CLS_V2 = 1, CLS_V4 = 2, CLS_F2 = 3, CLS_LDS = 4, CLS_TILE = 5, kClasses = 6 };
+constexpr int kStripClasses = 5;  // those a tile shape of the C ABI has heights for
+static const int kVecOfClass[kClasses] = {1, 2, 4, 2, 2, 1};
+static const int kStepsOfClass[kStripClasses] = {1, 1, 1, 2, 0};  // 0: every step of the burst in one launch
 
 // How grids are assigned to classes.  MIXED: the fused class except for grids of
 // the four-column class narrower than kMixedWide columns (measured on the uneven
@@ -97,7 +92,7 @@ struct lbt1_batch {
   int2 *h_ranges = nullptr;
   std::vector<int2> items[lbt1::kClasses];
   std::vector<int2> ritems;
-  int rows[lbt1::kClasses] = {14, 14, 14, 14, 6};  // strip height per class
+  int rows[lbt1::kClasses] = {14, 14, 14, 14, 6, 0};  // strip height per class
   int blocks[lbt1::kClasses] = {};                  // launch size per class
   size_t lds_bytes = 0;                             // dynamic LDS of the LDS-class launch
   size_t lds_limit = 0;                             // most LDS one workgroup may take
@@ -106,6 +101,9 @@ struct lbt1_batch {
   bool lds_mode = false;
   int vec_cap_class = lbt1::CLS_V4;  // widest one-step class a grid may take
   int want_rows[lbt1::kClasses] = {};
+  bool tiles = true;                        // every grid in the tile class (no strip shape asked for)
+  const lbt1::BatchTileKernel *tile = nullptr;  // region shape and steps of a launch of the tile class
+  int tile_steps = 8;
   bool items_dirty = true;
   hipGraphExec_t graph = nullptr;
   int graph_K = 0, graph_mask = -1;
@@ -114,6 +112,15 @@ struct lbt1_batch {
 };
 
 namespace lbt1 {
+
+// launches a class takes for a burst of K steps, and the parity flips of a grid of
+// the class that takes k steps in it
+static int class_steps(const lbt1_batch *b, int c) { return c == CLS_TILE ? b->tile_steps : kStepsOfClass[c]; }
+static int class_launches(const lbt1_batch *b, int c, int K) {
+  const int k = class_steps(b, c);
+  return k ? (K + k - 1) / k : 1;
+}
+static int class_flips(const lbt1_batch *b, int c, int k) { return k <= 0 ? 0 : class_launches(b, c, k); }
 
 static const int kCntActive = 6, kCntRitems = 7;  // slots of d_counts after the class counts
 
@@ -134,6 +141,7 @@ static int chunks_of(int nx, int v) { return (nx + v - 1) / v; }
 // whose rows two columns per lane fit (all of them, or those narrower than the
 // four-column class), the others their widest one-step class.
 static int class_for(const lbt1_batch *b, const Slot &sl) {
+  if (b->tiles) return CLS_TILE;
   const bool fits2 = sl.g->nx % 2 == 0 || !(sl.g->periodic & 1u);
   if (b->lds_mode && fits2 && batch_lds_kernel(sl.g->prec, 6) &&
       (size_t)lds_grid_bytes(sl.g->nx, sl.g->ny, 2, (int)value_bytes(sl.g->prec)) <= b->lds_limit)
@@ -146,6 +154,7 @@ static int class_for(const lbt1_batch *b, const Slot &sl) {
 }
 
 static const void *class_kernel(const lbt1_batch *b, int c) {
+  if (c == CLS_TILE) return b->tile ? b->tile->fn : nullptr;
   if (c == CLS_LDS) return batch_lds_kernel(b->prec, b->rows[c]);
   return c == CLS_F2 ? batch_fused_kernel(b->prec, b->rows[c]) : batch_step_kernel(b->prec, c, b->rows[c]);
 }
@@ -154,6 +163,13 @@ static const void *class_kernel(const lbt1_batch *b, int c) {
 // use lets every CU hold at once, but no more than the class has work items
 // for (each block takes four strips per pass).
 static int class_blocks(const lbt1_batch *b, int c) {
+  if (c == CLS_TILE) {
+    // one block per tile, rounded up to a quarter of a power of two, so that admitting or
+    // finishing a grid seldom changes the graph (the blocks past the list end at once)
+    long q = 8;
+    while (4 * q < (long)b->items[c].size()) q *= 2;
+    return (int)(((long)b->items[c].size() + q - 1) / q * q);
+  }
   const void *fn = class_kernel(b, c);
   int per_cu = 2;
   const size_t shmem = c == CLS_LDS ? b->lds_bytes : 0;
@@ -167,10 +183,40 @@ static int class_blocks(const lbt1_batch *b, int c) {
 static long graph_shape(const lbt1_batch *b) {
   long key = 0;
   for (int c = 0; c < kClasses; ++c) key = key * 1000003L + b->rows[c] * 100003L + b->blocks[c];
+  key = key * 1000003L + b->tile_steps;
+  if (b->tile) key = key * 1000003L + b->tile->vec * 100L + b->tile->rows;
   return key * 1000003L + (long)b->lds_bytes;
 }
 
+// Region shape and steps per launch of the tile class: the least modelled time of a step
+// over the tiles of all resident grids.
+static void choose_tile(lbt1_batch *b) {
+  double best = 1e300;
+  for (int i = 0; const BatchTileKernel *t = batch_tile_kernel(b->prec, i); ++i)
+    for (int steps : {4, 6, 8, 10, 12}) {
+      const StepKernel *k = find_tile(KIND_TILE, b->prec, true, WALL_PAPER, t->vec, t->rows, t->threads / 64);
+      lbt1_kernel_config c{};
+      c.vec = t->vec;
+      c.rows = t->rows;
+      long tiles = 0;
+      bool ok = k != nullptr;
+      for (const Slot &sl : b->slots) {
+        TileMap m;
+        if (sl.state == LBT1_SLOT_FREE) continue;
+        ok = ok && tile_map(sl.g->nx, sl.g->ny, sl.g->periodic, c, steps, &m);
+        if (ok) tiles += m.tiles;
+      }
+      const double us = ok ? tile_us(*k, steps, tiles, b->cus) : 1e300;
+      if (us < best) {
+        best = us;
+        b->tile = t;
+        b->tile_steps = steps;
+      }
+    }
+}
+
 static void rebuild_items(lbt1_batch *b) {
+  if (b->tiles && b->prec >= 0) choose_tile(b);
   long tall[kClasses] = {};
   long tall30 = 0;  // fused-class strips at 30 rows
   for (int s = 0; s < b->max_slots; ++s) {
@@ -191,7 +237,7 @@ static void rebuild_items(lbt1_batch *b) {
     b->rows[c] = b->want_rows[c] ? b->want_rows[c] : c == CLS_LDS || tall[c] < 8L * b->cus ? 6 : 14;
     if (c == CLS_F2 && !b->want_rows[c] && tall30 >= 4L * b->cus) b->rows[c] = 30;
     // a height the batch's precision has no kernel for (30 rows in FP64) falls back
-    if (b->prec >= 0 && !class_kernel(b, c)) b->rows[c] = 14;
+    if (c != CLS_TILE && b->prec >= 0 && !class_kernel(b, c)) b->rows[c] = 14;
   }
   // (block counts are set below, once the lists are built)
   b->ritems.clear();
@@ -203,9 +249,22 @@ static void rebuild_items(lbt1_batch *b) {
     const int v = kVecOfClass[sl.cls];
     const int rows = b->rows[sl.cls];
     const int sx = (chunks_of(sl.g->nx, v) + 61) / 62;  // strips of 62 chunks of v columns
-    const int sy = (sl.g->ny + rows - 1) / rows;
+    const int sy = rows ? (sl.g->ny + rows - 1) / rows : 0;
     b->h_grids[s].strips_x = sx;
-    if (sl.cls == CLS_LDS) {
+    if (sl.cls == CLS_TILE) {
+      TileMap m;
+      lbt1_kernel_config c{};
+      c.vec = b->tile->vec;
+      c.rows = b->tile->rows;
+      (void)tile_map(sl.g->nx, sl.g->ny, sl.g->periodic, c, b->tile_steps, &m);
+      BatchGrid &d = b->h_grids[s];
+      d.strips_x = m.tiles_x;
+      d.hx = m.hx;
+      d.hy = m.hy;
+      d.ox = m.ox;
+      d.oy = m.oy;
+      for (int k = 0; k < m.tiles; ++k) b->items[sl.cls].push_back(make_int2(s, k));
+    } else if (sl.cls == CLS_LDS) {
       // one item per grid: its workgroup walks all of its strips
       b->items[sl.cls].push_back(make_int2(s, 0));
       b->lds_bytes = std::max(b->lds_bytes, (size_t)lds_grid_bytes(sl.g->nx, sl.g->ny, 2, (int)value_bytes(sl.g->prec)));
@@ -294,17 +353,18 @@ static lbt1_status build_graph(lbt1_batch *b, int K, int mask) {
   for (int c = 0; c < kClasses && !st; ++c) {
     if (!(mask & (1 << c))) continue;
     hipGraphNode_t prev = nullptr;
-    const int launches = class_launches(c, K);
+    const int launches = class_launches(b, c, K);
     for (int s = 0; s < launches && !st; ++s) {
       BatchStepArgs a;
       a.grids = b->d_grids;
       a.items = b->d_items[c];
       a.count = b->d_counts + c;
       a.step = s;
+      a.steps = class_steps(b, c);
       argv.push_back(a);
       void *args[] = {&argv.back()};
       hipGraphNode_t node;
-      st = add(class_kernel(b, c), dim3(b->blocks[c]), dim3(256), args, &prev, prev ? 1 : 0, &node,
+      st = add(class_kernel(b, c), dim3(b->blocks[c]), dim3(c == CLS_TILE ? b->tile->threads : 256), args, &prev, prev ? 1 : 0, &node,
                c == CLS_LDS ? b->lds_bytes : 0);
       prev = node;
     }
@@ -377,7 +437,7 @@ static lbt1_status launch_burst(lbt1_batch *b, int K, int *nact_out) {
   }
   for (int k = 0; k < nact; ++k) {
     const int s = b->h_active[k];
-    b->h_grids[s].flips = class_flips(b->slots[s].cls, b->slots[s].steps_this_burst);
+    b->h_grids[s].flips = class_flips(b, b->slots[s].cls, b->slots[s].steps_this_burst);
   }
   int mask = 0;
   for (int c = 0; c < kClasses; ++c)
@@ -391,7 +451,7 @@ static lbt1_status launch_burst(lbt1_batch *b, int K, int *nact_out) {
   if (rebuilt) {
     // the kind of every strip of the new lists (stream-ordered before the burst)
     for (int c = 0; c < kClasses; ++c) {
-      if (c == CLS_LDS || b->items[c].empty()) continue;
+      if (c == CLS_LDS || c == CLS_TILE || b->items[c].empty()) continue;
       BatchClassifyArgs ca;
       ca.grids = b->d_grids;
       ca.items = b->d_items[c];
@@ -420,7 +480,7 @@ static lbt1_status set_shape(lbt1_batch *b, const lbt1_batch_shape &sh) {
   if (sh.lds != 0 && sh.lds != 1) return fail(LBT1_EINVAL, "lds mode %d", sh.lds);
   if (sh.vec_cap != 0 && sh.vec_cap != 1 && sh.vec_cap != 2 && sh.vec_cap != 4)
     return fail(LBT1_EINVAL, "vec_cap %d (0, 1, 2 or 4)", sh.vec_cap);
-  for (int c = 0; c < kClasses; ++c) {
+  for (int c = 0; c < kStripClasses; ++c) {
     const int r = sh.rows[c];
     if (r == 0) continue;
     const int pr = b->prec >= 0 ? b->prec : LBT1_F32;
@@ -432,7 +492,11 @@ static lbt1_status set_shape(lbt1_batch *b, const lbt1_batch_shape &sh) {
   b->fuse_mode = sh.fuse;
   b->lds_mode = sh.lds != 0;
   b->vec_cap_class = sh.vec_cap == 1 ? CLS_V1 : sh.vec_cap == 2 ? CLS_V2 : CLS_V4;
-  for (int c = 0; c < kClasses; ++c) b->want_rows[c] = sh.rows[c];
+  for (int c = 0; c < kStripClasses; ++c) b->want_rows[c] = sh.rows[c];
+  // the default shape (mixed, heights and columns left to the library) leaves the classes
+  // to the library too: the tile class
+  b->tiles = sh.fuse == FUSE_MIXED && !b->lds_mode && b->vec_cap_class == CLS_V4;
+  for (int c = 0; c < kStripClasses; ++c) b->tiles &= sh.rows[c] == 0;
   b->items_dirty = true;
   return LBT1_OK;
 }
@@ -606,7 +670,7 @@ lbt1_status lbt1_batch_get_shape(lbt1_batch *b, lbt1_batch_shape *shape) {
   if (b->items_dirty) rebuild_items(b);  // the heights the heuristic gives the resident grids now
   shape->fuse = b->fuse_mode;
   shape->lds = b->lds_mode ? 1 : 0;
-  for (int c = 0; c < kClasses; ++c) shape->rows[c] = b->rows[c];
+  for (int c = 0; c < kStripClasses; ++c) shape->rows[c] = b->tiles ? 0 : b->rows[c];
   shape->vec_cap = kVecOfClass[b->vec_cap_class];
   return LBT1_OK;
 }
@@ -649,6 +713,7 @@ lbt1_status lbt1_batch_autotune(lbt1_batch *b, int32_t burst_steps, int32_t reps
   const int saved_mode = b->fuse_mode;
   const bool saved_lds = b->lds_mode;
   const int saved_cap = b->vec_cap_class;
+  const bool saved_tiles = b->tiles;
   int saved_rows[kClasses];
   std::memcpy(saved_rows, b->want_rows, sizeof saved_rows);
   hipEvent_t e0, e1;
@@ -672,6 +737,10 @@ lbt1_status lbt1_batch_autotune(lbt1_batch *b, int32_t burst_steps, int32_t reps
   };
   lbt1_batch_shape bestsh{};
   double best_ms = 1e300;
+  // the default shape: the tile class
+  bestsh.fuse = FUSE_MIXED;
+  bestsh.vec_cap = 4;
+  best_ms = time_shape(bestsh);
   const int modes[] = {FUSE_NONE, FUSE_MIXED, FUSE_ALL};
   // every column cap (four, then two columns per lane), LDS mode and fuse mode
   for (int cap = CLS_V4; cap >= CLS_V2 && !st; --cap) {
@@ -682,6 +751,7 @@ lbt1_status lbt1_batch_autotune(lbt1_batch *b, int32_t burst_steps, int32_t reps
       b->fuse_mode = mode;
       b->lds_mode = lds != 0;
       b->vec_cap_class = CLS_V4;
+      b->tiles = false;
       bool present[kClasses] = {}, wide = false;
       for (int s : res) {
         const int c = class_for(b, b->slots[s]);
@@ -702,9 +772,13 @@ lbt1_status lbt1_batch_autotune(lbt1_batch *b, int32_t burst_steps, int32_t reps
       cur.fuse = mode;
       cur.lds = lds;
       cur.vec_cap = kVecOfClass[cap];
-      double cur_ms = time_shape(cur);
+      // (the mixed shape without a height is the default, timed above)
+      double cur_ms = mode == FUSE_MIXED && !lds && cap == CLS_V4 ? 1e300 : time_shape(cur);
+      if (cur_ms >= 1e300)
+        for (int c = 0; c < kStripClasses; ++c)
+          if (present[c] && c != CLS_LDS) cur.rows[c] = 14;  // a first height to descend from
       // coordinate descent over the strip height of each class present
-      for (int c = 0; c < kClasses && !st; ++c) {
+      for (int c = 0; c < kStripClasses && !st; ++c) {
         if (!present[c]) continue;
         const int single[] = {6, 14, 30};
         const int fused[] = {2, 6, 14, 30};
@@ -741,6 +815,7 @@ lbt1_status lbt1_batch_autotune(lbt1_batch *b, int32_t burst_steps, int32_t reps
     b->fuse_mode = saved_mode;
     b->lds_mode = saved_lds;
     b->vec_cap_class = saved_cap;
+    b->tiles = saved_tiles;
     std::memcpy(b->want_rows, saved_rows, sizeof saved_rows);
     b->items_dirty = true;
     if (st) return st;

@@ -9,7 +9,8 @@ namespace lbt1 {
 // every burst).  parity0 is the grid's parity at the start of the burst;
 // the grid takes steps_left (<= burst length) steps in this burst, in `flips`
 // launches (each launch reads one parity and writes the other: one launch per
-// step, one per two steps in the fused class, one per burst in the LDS class).
+// step, one per two steps in the fused class, one per tile_steps in the tile class, one
+// per burst in the LDS class).
 struct BatchGrid {
   void *plane[2][3];
   const uint8_t *flags;
@@ -19,7 +20,8 @@ struct BatchGrid {
   int parity0;
   int steps_left;
   int flips;
-  int strips_x;  // strips per row band (columns of 64 * vec)
+  int strips_x;  // strips per row band (columns of 64 * vec); tile class: tiles per row of tiles
+  int hx, hy, ox, oy;  // tile class: halo and stored nodes of a tile (TileMap)
   double fx, fy, sc_d, sc_j, is_d, is_j;
   void *trash;  // see StepArgs::trash
 };
@@ -41,9 +43,10 @@ enum { STRIP_WALLS = 0, STRIP_COLUMN_WALLS = 1, STRIP_INTERIOR = 2 };
 
 struct BatchStepArgs {
   const BatchGrid *grids;
-  const int2 *items;  // (slot, 4 * strip + kind); the LDS class: (slot, 0)
+  const int2 *items;  // (slot, 4 * strip + kind); the LDS class: (slot, 0); the tile class: (slot, tile)
   const int *count;   // number of items (device memory, so a graph need not change)
-  int step;           // step index inside the burst
+  int step;           // launch index inside the burst
+  int steps;          // tile class: steps of a launch
 };
 
 struct BatchClassifyArgs {

@@ -7,6 +7,7 @@
 #include "lbt1_fused.hpp"
 #include "lbt1_fused_wall.hpp"
 #include "lbt1_step.hpp"
+#include "lbt1_tile.hpp"
 
 namespace lbt1 {
 
@@ -351,6 +352,51 @@ __global__ void __launch_bounds__(256) k_step_batch_lds(BatchStepArgs b) {
       if (x < nx) static_cast<S *>(g.plane[1 - p][q])[(long)y * g.rs + x] = fin[i];
     }
     __syncthreads();  // the next grid of this block reuses the LDS
+  }
+}
+
+}  // namespace lbt1
+
+namespace lbt1 {
+
+// The tile class: launch s of a burst takes steps s * b.steps ... of every grid (fewer where
+// a grid has fewer left), each block one tile of one grid, held in registers as in
+// k_step_tile.  A launch costs the same whatever it covers, and uneven grids of 32 to 512
+// nodes a side fill the chip poorly one or two steps at a time: 40 cavities in FP16S take
+// 4 to 6 steps a launch here instead of one and two in two chains of launches.
+template <int P, int W, int CPL, int RPT, int THREADS>
+__global__ void __launch_bounds__(THREADS) k_step_batch_tile(BatchStepArgs b) {
+  __shared__ __align__(16) TileShared<typename Traits<P>::C, THREADS * CPL> sh;
+  // XCD x takes a contiguous range of the items (see tile_of)
+  const int n = *b.count, per = (n + 7) / 8;
+  const int it = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
+  if ((int)(blockIdx.x >> 3) >= per || it >= n) return;  // uniform across the block
+  const int2 item = b.items[it];
+  const BatchGrid &g = b.grids[item.x];
+  const int left = g.steps_left - b.steps * b.step;
+  if (left <= 0) return;
+  const StepArgs a = batch_step_args(g, (g.parity0 + b.step) & 1);
+  TileMap m;
+  m.steps = min(left, b.steps);
+  m.hx = g.hx;
+  m.hy = g.hy;
+  m.ox = g.ox;
+  m.oy = g.oy;
+  m.tiles_x = g.strips_x;
+  const bool unit = !Traits<P>::kScaled || (a.sc_d == 1.0 && a.sc_j == 1.0 && a.is_d == 1.0 && a.is_j == 1.0);
+  // 16-bit storage: four bodies with their conditions in scalar registers ran 19-43 % longer
+  // (40 and 512 cavities) than with masks; the single-grid kernels, of two, run shorter
+  constexpr bool CONDS = !Traits<P>::kScaled;
+  if (g.wall == WALL_PAPER) {
+    if (unit)
+      tile_body<P, true, WALL_PAPER, W, CPL, RPT, THREADS, true, CONDS>(a, m, item.y, sh);
+    else
+      tile_body<P, true, WALL_PAPER, W, CPL, RPT, THREADS, false, CONDS>(a, m, item.y, sh);
+  } else {
+    if (unit)
+      tile_body<P, true, WALL_HALFWAY, W, CPL, RPT, THREADS, true, CONDS>(a, m, item.y, sh);
+    else
+      tile_body<P, true, WALL_HALFWAY, W, CPL, RPT, THREADS, false, CONDS>(a, m, item.y, sh);
   }
 }
 

@@ -23,6 +23,9 @@ const BatchKernels &batch_kernels<LBT1_PREC>() {
        {nullptr, nullptr, nullptr}},
       {BATCH_FUSED(2), BATCH_FUSED(6), BATCH_FUSED(14), nullptr},
       {nullptr, nullptr},
+      {{32, 32, 512, (const void *)&k_step_batch_tile<LBT1_PREC, 32, 1, 2, 512>},
+       {64, 32, 512, (const void *)&k_step_batch_tile<LBT1_PREC, 64, 1, 4, 512>},
+       {0, 0, 0, nullptr}},
 #else
       // strips of 6 rows (short: half the serial latency of a strip, for classes with
       // too few strips to fill the device), 14 rows (tall) and 30 rows (fewer, longer
@@ -32,6 +35,9 @@ const BatchKernels &batch_kernels<LBT1_PREC>() {
        {BATCH_STEP(1, 30), BATCH_STEP(2, 30), BATCH_STEP(4, 30)}},
       {BATCH_FUSED(2), BATCH_FUSED(6), BATCH_FUSED(14), BATCH_FUSED(30)},
       {(const void *)&k_step_batch_lds<LBT1_PREC, 2, 6>, (const void *)&k_step_batch_lds<LBT1_PREC, 2, 14>},
+      {{32, 32, 1024, (const void *)&k_step_batch_tile<LBT1_PREC, 32, 1, 1, 1024>},
+       {64, 32, 1024, (const void *)&k_step_batch_tile<LBT1_PREC, 64, 1, 2, 1024>},
+       {64, 64, 512, (const void *)&k_step_batch_tile<LBT1_PREC, 64, 1, 8, 512>}},
 #endif
       (const void *)&k_reduce_batch<LBT1_PREC>};
   return k;

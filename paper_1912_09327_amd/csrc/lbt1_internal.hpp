@@ -30,10 +30,16 @@ struct PrecKernels {
   int count;
   const void *reduce_partial, *bgk_psi, *bgk_reduce_partial;
 };
+struct BatchTileKernel {  // regions of vec columns by `rows` rows on `threads` threads
+  int vec, rows, threads;
+  const void *fn;
+};
+constexpr int kBatchTiles = 3;
 struct BatchKernels {
   const void *step[3][3];  // [strips of 6, 14, 30 rows][1, 2, 4 columns per lane]
   const void *fused[4];    // strips of 2, 6, 14, 30 rows
   const void *lds[2];      // strips of 6, 14 rows
+  BatchTileKernel tile[kBatchTiles];
   const void *reduce;
 };
 template <int P> const PrecKernels &prec_kernels();
@@ -61,6 +67,7 @@ const void *bgk_psi_kernel(int prec);
 const void *batch_step_kernel(int prec, int vec_class, int rows);
 const void *batch_fused_kernel(int prec, int rows);  // two steps per launch, two columns per lane
 const void *batch_lds_kernel(int prec, int rows);    // grids resident in LDS for a burst
+const BatchTileKernel *batch_tile_kernel(int prec, int i);  // regions held in registers; NULL past the last
 const void *batch_reduce_kernel(int prec);
 const void *batch_classify_kernel(int vec);          // strip kinds of a work list, once per list
 const void *batch_reduce_final_kernel();

@@ -155,6 +155,11 @@ const void *batch_lds_kernel(int prec, int rows) {
   return rows == 6 ? k->lds[0] : rows == 14 ? k->lds[1] : nullptr;
 }
 
+const BatchTileKernel *batch_tile_kernel(int prec, int i) {
+  const BatchKernels *k = batch_of_prec(prec);
+  return k && i >= 0 && i < kBatchTiles && k->tile[i].fn ? &k->tile[i] : nullptr;
+}
+
 const void *batch_reduce_kernel(int prec) { return batch_of_prec(prec) ? batch_of_prec(prec)->reduce : nullptr; }
 
 const void *batch_classify_kernel(int vec) {

@@ -244,7 +244,7 @@ static bool strip_fits(int nx, int vec, bool periodic_x) { return vec >= 1 && (n
 static int chunks_of(int nx, int vec) { return (nx + vec - 1) / vec; }
 
 // The tile kernel of a kind with regions of w columns and `rows` rows on `waves` wavefronts.
-static const StepKernel *find_tile(int kind, int prec, bool haswall, int wall, int w, int rows, int waves) {
+const StepKernel *find_tile(int kind, int prec, bool haswall, int wall, int w, int rows, int waves) {
   int n = 0;
   const StepKernel *t = step_kernels(&n);
   for (int i = 0; i < n; ++i) {
@@ -284,13 +284,11 @@ static std::tuple<int, int, int, int, int, int> tune_key(const lbt1_grid *g) {
 // rows of the region, `waves` wavefronts of a block, `fuse` steps of a launch.
 static bool is_tile(const lbt1_kernel_config &c) { return c.kernel == LBT1_KERNEL_STRIP && c.vec >= 32; }
 
-// Most steps of one launch of a tile kernel (the steps of a graph burst).
-constexpr int kMaxTileSteps = 64;
 
 // Tiles of configuration c on an nx x ny grid for a launch of `steps` steps: a halo
 // of that many nodes on each side of an axis, none on an axis that is not periodic and
 // fits the region whole.  False when the halo leaves nothing to store.
-static bool tile_map(int nx, int ny, uint32_t periodic, const lbt1_kernel_config &c, int steps, TileMap *m) {
+bool tile_map(int nx, int ny, uint32_t periodic, const lbt1_kernel_config &c, int steps, TileMap *m) {
   m->steps = steps;
   const int even = (steps + 1) / 2 * 2;  // chunks of two columns start at even columns
   m->hx = !(periodic & 1u) && nx <= c.vec ? 0 : c.vec > 64 ? even : steps;
@@ -310,10 +308,17 @@ static dim3 tile_grid(const TileMap &m) { return dim3(8 * (unsigned)m.per_xcd, 1
 // of a launch widens the halo by a node; three and fewer measured slower on every grid.
 static const int kTileSteps[] = {4, 6, 8, 10, 12, 16, kMaxTileSteps};
 
+// Modelled us per step of a tile kernel on `tiles` blocks: a launch takes us_launch and, for
+// each block that falls to the busiest CU (past eight rounds the average: blocks end at
+// different times), us_step per step and us_block.
+double tile_us(const StepKernel &k, int steps, long tiles, int cus) {
+  const double per_cu = (double)tiles / cus;
+  const double rounds = per_cu <= 8 ? std::ceil(per_cu) : per_cu + 0.5;
+  return (k.us_launch + rounds * (steps * k.us_step + k.us_block)) / steps;
+}
+
 // The tile kernel of a kind and the steps per launch with the least modelled time per
-// step, which goes to *us_out.  A launch takes us_launch and, for each block that falls to
-// the busiest CU (past eight rounds the average: blocks end at different times), us_step
-// per step and us_block.  On 80 grids of 48^2 to 8192^2, periodic and cavities, FP64,
+// step (tile_us), which goes to *us_out.  On 80 grids of 48^2 to 8192^2, periodic and cavities, FP64,
 // FP32 and FP16S, what it picks is within 2 % of the fastest shape on average.
 static lbt1_kernel_config tile_choice(int kind, int prec, bool haswall, int wall, int nx, int ny, uint32_t periodic, int cus,
                                       double *us_out) {
@@ -334,9 +339,7 @@ static lbt1_kernel_config tile_choice(int kind, int prec, bool haswall, int wall
       c.fuse = steps;
       TileMap m;
       if (!tile_map(nx, ny, periodic, c, steps, &m)) continue;
-      const double per_cu = (double)m.tiles / cus;
-      const double rounds = per_cu <= 8 ? std::ceil(per_cu) : per_cu + 0.5;
-      const double us = (k.us_launch + rounds * (steps * k.us_step + k.us_block)) / steps;
+      const double us = tile_us(k, steps, m.tiles, cus);
       if (us < best_us) {
         best_us = us;
         best = c;

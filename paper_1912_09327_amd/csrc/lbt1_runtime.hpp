@@ -96,4 +96,10 @@ lbt1_status bind_config(lbt1_grid *g, const lbt1_kernel_config &want, int cus);
 StepArgs step_args(const lbt1_grid *g, int src_parity);
 lbt1_status enqueue_steps(lbt1_grid *g, int64_t n, hipStream_t s, bool use_graph);
 lbt1_status enqueue_reduce(lbt1_grid *g, uint32_t what, hipStream_t s);
+// tile kernels (lbt1_tile.hpp, lbt1_bgk_tile.hpp): most steps of one launch, the kernel of a
+// shape, the tiles of a grid, the modelled time of a step
+constexpr int kMaxTileSteps = 64;
+const StepKernel *find_tile(int kind, int prec, bool haswall, int wall, int w, int rows, int waves);
+bool tile_map(int nx, int ny, uint32_t periodic, const lbt1_kernel_config &c, int steps, TileMap *m);
+double tile_us(const StepKernel &k, int steps, long tiles, int cus);
 }  // namespace lbt1

@@ -134,7 +134,7 @@ __device__ __forceinline__ int tile_of(const TileMap &m) {
   return (int)(blockIdx.x & 7) * m.per_xcd + (int)(blockIdx.x >> 3);
 }
 
-template <int P, int WALL, int W, int CPL, int RPT, int THREADS, bool UNIT>
+template <int P, int WALL, int W, int CPL, int RPT, int THREADS, bool UNIT, bool CONDS>
 struct TileRegion {
   using T = Traits<P>;
   using C = typename T::C;
@@ -264,15 +264,20 @@ struct TileRegion {
   // source along e_q is a wall; fluid: a bit per node (node i * CPL + c).  An arrival from
   // a wall is replaced by the target's own value before it is summed.
   static constexpr int kWords = (RPT * CPL + 3) / 4;
+  // with one or two nodes a thread their 18 conditions stay in scalar registers over the
+  // loop: one vector operation a select instead of two
+  static constexpr bool kConditions = CONDS && RPT * CPL <= 2;
   __device__ __forceinline__ void march_walls(Shared &sh, const int steps, uint32_t (&from_wall)[kWords], uint32_t fluid) {
     constexpr bool HALF = WALL == WALL_HALFWAY;
     for (int s = 0; s < steps; ++s) {
       C(*const e)[NODES] = sh.v[s % Shared::kCopies];
-      // (the masks are formed anew in every step: kept over the loop they would take a
-      // register each)
+      if (!kConditions) {
+        // the masks are formed anew in every step: kept over the loop they would take a
+        // register each
 #pragma unroll
-      for (int k = 0; k < kWords; ++k) asm volatile("" : "+v"(from_wall[k]));
-      asm volatile("" : "+v"(fluid));
+        for (int k = 0; k < kWords; ++k) asm volatile("" : "+v"(from_wall[k]));
+        asm volatile("" : "+v"(fluid));
+      }
       C l0[CPL], x0[CPL], w0[CPL], v0[CPL];
       C ps[CPL], px[CPL], pu[CPL];
       C u[CPL][3];                                        // arrivals of the newest row in the row below
@@ -283,10 +288,18 @@ struct TileRegion {
       auto sel = [&](const int i, const int c, const int q, const C arrived, const C sent_back)
           __attribute__((always_inline)) -> C {
         const C v = HALF ? sent_back : q <= 4 ? wall_axis<C>(d[i][c]) : wall_diag<C>(d[i][c]);
-        const int node = i * CPL + c;
-        return pick(spread(from_wall[node / 4], node % 4 * 8 + q - 1), v, arrived);
+        const int node = i * CPL + c, bit = node % 4 * 8 + q - 1;
+        if (kConditions) return (from_wall[node / 4] >> bit & 1u) ? v : arrived;
+        return pick(spread(from_wall[node / 4], bit), v, arrived);
       };
       auto store = [&](const int i, const int c, const C dn, const C xn, const C yn) __attribute__((always_inline)) {
+        if (kConditions) {
+          const bool on = fluid >> (i * CPL + c) & 1u;
+          d[i][c] = on ? dn : d[i][c];
+          jx[i][c] = on ? xn : jx[i][c];
+          jy[i][c] = on ? yn : jy[i][c];
+          return;
+        }
         const uint32_t live = spread(fluid, i * CPL + c);
         d[i][c] = pick(live, dn, d[i][c]);
         jx[i][c] = pick(live, xn, jx[i][c]);
@@ -392,10 +405,10 @@ struct TileRegion {
   }
 };
 
-template <int P, bool HASWALL, int WALL, int W, int CPL, int RPT, int THREADS, bool UNIT>
+template <int P, bool HASWALL, int WALL, int W, int CPL, int RPT, int THREADS, bool UNIT, bool CONDS = true>
 __device__ __forceinline__ void tile_body(
-    const StepArgs &a, const TileMap &m, const int tile, typename TileRegion<P, WALL, W, CPL, RPT, THREADS, UNIT>::Shared &sh) {
-  using R = TileRegion<P, WALL, W, CPL, RPT, THREADS, UNIT>;
+    const StepArgs &a, const TileMap &m, const int tile, typename TileRegion<P, WALL, W, CPL, RPT, THREADS, UNIT, CONDS>::Shared &sh) {
+  using R = TileRegion<P, WALL, W, CPL, RPT, THREADS, UNIT, CONDS>;
   using T = Traits<P>;
   using C = typename T::C;
   using S = typename T::S;

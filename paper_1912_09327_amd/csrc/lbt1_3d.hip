@@ -311,11 +311,8 @@ lbt1_status lbt1_grid3d_set_geometry(lbt1_grid3d *g, const uint8_t *flags, const
   hipError_t e;
   if ((e = hipSetDevice(g->device)) != hipSuccess) return hip_fail(e, "hipSetDevice");
   if ((e = hipStreamSynchronize(g->stream)) != hipSuccess) return hip_fail(e, "hipStreamSynchronize");
-  for (int p = 0; p < 2; ++p)
-    if ((e = hipMemcpy(g->base + (size_t)p * g->L.state, stage.data(), g->L.state, hipMemcpyHostToDevice)) != hipSuccess)
-      return hip_fail(e, "hipMemcpy H2D");
-  if (g->L.snap_off &&
-      (e = hipMemcpy(g->base + g->L.snap_off, stage.data(), g->L.state, hipMemcpyHostToDevice)) != hipSuccess)
+  if ((e = upload(g->base, stage.data(), g->L.state,
+                  {g->base + g->L.state, g->L.snap_off ? g->base + g->L.snap_off : nullptr}, g->stream)) != hipSuccess)
     return hip_fail(e, "hipMemcpy H2D");
   if ((e = hipMemcpy(g->flags, fstage.data(), fstage.size(), hipMemcpyHostToDevice)) != hipSuccess)
     return hip_fail(e, "hipMemcpy H2D");
@@ -381,25 +378,29 @@ lbt1_status lbt1_grid3d_read_moments(lbt1_grid3d *g, double *rho, double *jx, do
   if (!g->geometry) return fail(LBT1_ESTATE, "no geometry set");
   const int nx = g->nx, ny = g->ny, nz = g->nz;
   const size_t c = value_bytes(g->prec);
-  std::vector<char> stage;
-  try {
-    stage.resize((size_t)nx * ny * nz * c);
-  } catch (...) {
-    return fail(LBT1_ENOMEM, "host staging");
-  }
   hipError_t e;
   if ((e = hipSetDevice(g->device)) != hipSuccess) return hip_fail(e, "hipSetDevice");
   if ((e = hipStreamSynchronize(g->stream)) != hipSuccess) return hip_fail(e, "hipStreamSynchronize");
   double *dst[4] = {rho, jx, jy, jz};
-  for (int m = 0; m < 4; ++m) {
-    if (!dst[m]) continue;
-    // rows of all planes: ny * nz rows of nx values, row stride rs
-    if ((e = hipMemcpy2D(stage.data(), (size_t)nx * c, g->plane[g->parity][m], (size_t)g->L.rs * c, (size_t)nx * c,
-                         (size_t)ny * nz, hipMemcpyDeviceToHost)) != hipSuccess)
-      return hip_fail(e, "hipMemcpy2D D2H");
-    decode_values(g->prec, stage.data(), (size_t)nx * ny * nz, g->sc[m == 0 ? 0 : 1], dst[m]);
-    if (m == 0)
-      for (size_t i = 0; i < (size_t)nx * ny * nz; ++i) dst[m][i] += 1.0;
+  try {
+    // plane by plane, all four fields: one copy of the plane's adjacent rows
+    std::vector<char> stage(((size_t)(ny - 1) * g->L.rs + 3 * (size_t)g->L.pitch + nx) * c);
+    for (int z = 0; z < nz; ++z) {
+      const char *src = (const char *)g->plane[g->parity][0] + (size_t)z * g->L.zs * c;
+      if ((e = hipMemcpy(stage.data(), src, stage.size(), hipMemcpyDeviceToHost)) != hipSuccess)
+        return hip_fail(e, "hipMemcpy D2H");
+      for (int y = 0; y < ny; ++y)
+        for (int m = 0; m < 4; ++m) {
+          if (!dst[m]) continue;
+          double *row = dst[m] + ((size_t)z * ny + y) * nx;
+          decode_values(g->prec, stage.data() + ((size_t)y * g->L.rs + (size_t)m * g->L.pitch) * c, nx,
+                        g->sc[m == 0 ? 0 : 1], row);
+          if (m == 0)
+            for (int x = 0; x < nx; ++x) row[x] += 1.0;
+        }
+    }
+  } catch (...) {
+    return fail(LBT1_ENOMEM, "host staging");
   }
   return LBT1_OK;
 }

@@ -14,6 +14,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <initializer_list>
 #include <map>
 #include <mutex>
 #include <new>
@@ -126,42 +127,65 @@ static bool pow2_or_zero(double s) {
 }
 
 // ----------------------------------------------------------------- host codecs
-// Round a double to the nearest value with `mant` significand bits (round half
-// to even), normal exponent >= emin, gradual underflow below; returns +-inf
-// above `maxv`.  Used for IEEE binary16 (11 bits, emin -14, max 65504) and
-// bfloat16 (8 bits, emin -126, max (2 - 2^-7) 2^127).
-static double round_to_format(double x, int mant, int emin, double maxv) {
-  if (!std::isfinite(x) || x == 0.0) return x;
-  int e;
-  std::frexp(x, &e);               // x = m 2^e, 0.5 <= |m| < 1
-  int q = std::max(e, emin + 1) - mant;  // quantum exponent
-  double r = std::nearbyint(std::ldexp(x, -q));  // default rounding mode: to nearest even
-  double y = std::ldexp(r, q);
-  if (std::fabs(y) > maxv) return std::copysign(INFINITY, x);
-  return y;
+// The conversions below are written without branches and library calls, so that the loops
+// of encode_values and decode_values run several values at a time: one rounding from the
+// 64-bit value, half to even, gradual underflow, infinity above the largest value.
+//
+// A double rounded to MANT significand bits (at most 11) for exponents from EMIN up, to
+// the quantum of EMIN below: integer rounding of the fraction, or the addition of a number
+// whose unit in the last place is that quantum.
+constexpr double pow2(int e) { return e < 0 ? 0.5 * pow2(e + 1) : e > 0 ? 2.0 * pow2(e - 1) : 1.0; }
+template <int MANT, int EMIN>
+static inline double round_bits(double x) {
+  uint64_t u;
+  std::memcpy(&u, &x, 8);
+  constexpr int drop = 53 - MANT;
+  const uint64_t r = (u + (((u >> drop) & 1) + ((1ull << (drop - 1)) - 1))) & ~((1ull << drop) - 1);
+  double big;
+  std::memcpy(&big, &r, 8);
+  constexpr double magic = 1.5 * pow2(EMIN - (MANT - 1) + 52), least = pow2(EMIN);
+  const double tiny = (x + magic) - magic;
+  return std::fabs(x) < least ? tiny : big;
 }
 
-static uint16_t encode_half(double v) {
-  double r = round_to_format(v, 11, -14, 65504.0);
-  _Float16 h = (_Float16)(float)r;  // exact: r is representable
-  uint16_t b;
-  std::memcpy(&b, &h, 2);
-  return b;
+static inline uint16_t encode_half(double v) {
+  const double r = round_bits<11, -14>(v);
+  uint64_t u, uv;
+  std::memcpy(&u, &r, 8);
+  std::memcpy(&uv, &v, 8);
+  const uint16_t sign = (uint16_t)(uv >> 48) & 0x8000;
+  const double a = std::fabs(r);
+  const uint16_t normal = (uint16_t)((u >> 42) - (uint64_t)((1023 - 15) << 10)) & 0x7fff;
+  const uint16_t sub = (uint16_t)(int32_t)(a * 16777216.0);  // a < 2^-14: in units of 2^-24
+  uint16_t h = a < 6.103515625e-05 ? sub : normal;
+  h = a > 65504.0 ? (uint16_t)0x7c00 : h;
+  h = v != v ? (uint16_t)0x7e00 : h;
+  return sign | h;
 }
-static uint16_t encode_bf16(double v) {
-  if (std::isnan(v)) return 0x7fc0;
-  double r = round_to_format(v, 8, -126, std::ldexp(255.0, 120));
-  float f = (float)r;  // exact
+static inline uint16_t encode_bf16(double v) {
+  const double r = round_bits<8, -126>(v);
+  const float f = (float)r;  // exact, or infinite where r is past the largest value
+  uint32_t u;
+  uint64_t uv;
+  std::memcpy(&u, &f, 4);
+  std::memcpy(&uv, &v, 8);
+  const uint16_t sign = (uint16_t)(uv >> 48) & 0x8000;  // (a negative value that rounds to zero keeps it)
+  return v != v ? (uint16_t)0x7fc0 : (uint16_t)((u >> 16 & 0x7fff) | sign);
+}
+static inline double decode_half(uint16_t b) {
+  // exponent and fraction as those of a float, scaled by 2^112; 31 becomes 255
+  const uint32_t e = (uint32_t)(b & 0x7fff) << 13;
+  float f;
+  std::memcpy(&f, &e, 4);
+  f *= 5.192296858534828e33f;  // 2^112
   uint32_t u;
   std::memcpy(&u, &f, 4);
-  return (uint16_t)(u >> 16);
+  u = (b & 0x7c00) == 0x7c00 ? (e | 0x7f800000u) : u;
+  u |= (uint32_t)(b & 0x8000) << 16;
+  std::memcpy(&f, &u, 4);
+  return (double)f;
 }
-static double decode_half(uint16_t b) {
-  _Float16 h;
-  std::memcpy(&h, &b, 2);
-  return (double)(float)h;
-}
-static double decode_bf16(uint16_t b) {
+static inline double decode_bf16(uint16_t b) {
   uint32_t u = (uint32_t)b << 16;
   float f;
   std::memcpy(&f, &u, 4);
@@ -216,6 +240,33 @@ void decode_values(int prec, const void *in, size_t n, double scale, double *out
       break;
     }
   }
+}
+
+// ----------------------------------------------------------------- host copies
+// `bytes` from host memory to `dst` and, on the device, to each of the `more` places after
+// it (host memory crosses the bus once).
+hipError_t upload(void *dst, const void *host, size_t bytes, std::initializer_list<void *> more, hipStream_t s) {
+  hipError_t e = hipMemcpy(dst, host, bytes, hipMemcpyHostToDevice);
+  for (void *p : more)
+    if (e == hipSuccess && p) e = hipMemcpyAsync(p, dst, bytes, hipMemcpyDeviceToDevice, s);
+  return e == hipSuccess ? hipStreamSynchronize(s) : e;
+}
+
+// A window of `w` values by `h` rows (row stride `stride`, value size c) into `stage`, and the
+// position of row r in it, r * *pitch.  A strided copy goes row by row at about 20 us each
+// (701 rows: 15 ms); whole rows go as one copy, at 8 GB/s or more, so they do unless the window
+// is much narrower than its rows.
+hipError_t fetch_window(std::vector<char> &stage, const void *src, size_t w, size_t h, size_t stride, size_t c,
+                        size_t *pitch) {
+  const size_t whole = ((h - 1) * stride + w) * c;
+  if (h > 1 && whole < h * 160000) {
+    stage.resize(whole);
+    *pitch = stride * c;
+    return hipMemcpy(stage.data(), src, whole, hipMemcpyDeviceToHost);
+  }
+  stage.resize(w * h * c);
+  *pitch = w * c;
+  return hipMemcpy2D(stage.data(), w * c, src, stride * c, w * c, h, hipMemcpyDeviceToHost);
 }
 
 // ----------------------------------------------------------------- device check
@@ -904,9 +955,8 @@ static lbt1_status set_geometry_pop(lbt1_grid *g, const uint8_t *flags, const do
   hipError_t e;
   if ((e = hipSetDevice(g->device)) != hipSuccess) return hip_fail(e, "hipSetDevice");
   if ((e = hipStreamSynchronize(g->stream)) != hipSuccess) return hip_fail(e, "hipStreamSynchronize");
-  for (int p = 0; p < 2; ++p)
-    if ((e = hipMemcpy(g->base + (size_t)p * g->L.state, stage.data(), g->L.state, hipMemcpyHostToDevice)) != hipSuccess)
-      return hip_fail(e, "hipMemcpy H2D");
+  if ((e = upload(g->base, stage.data(), g->L.state, {g->base + g->L.state}, g->stream)) != hipSuccess)
+    return hip_fail(e, "hipMemcpy H2D");
   if (g->snap[0] && (e = hipMemcpy(g->base + g->L.snap_off, sstage.data(), sstage.size(), hipMemcpyHostToDevice)) != hipSuccess)
     return hip_fail(e, "hipMemcpy H2D");
   if ((e = hipMemcpy(g->flags, fstage.data(), plane, hipMemcpyHostToDevice)) != hipSuccess)
@@ -914,31 +964,48 @@ static lbt1_status set_geometry_pop(lbt1_grid *g, const uint8_t *flags, const do
   return LBT1_OK;
 }
 
+// The stored values of fields 0 .. nf - 1 of the current parity in rows y0 .. y0+h-1,
+// columns x0 .. x0+w-1: take(q, y, row) for each field and row, once the stream is done.
+template <typename F>
+static lbt1_status read_fields(lbt1_grid *g, int nf, int x0, int y0, int w, int h, const F &take) {
+  const size_t c = value_bytes(g->prec);
+  hipError_t e;
+  if ((e = hipSetDevice(g->device)) != hipSuccess) return hip_fail(e, "hipSetDevice");
+  if ((e = hipStreamSynchronize(g->stream)) != hipSuccess) return hip_fail(e, "hipStreamSynchronize");
+  try {
+    std::vector<char> stage;
+    size_t pitch = 0;
+    // interleaved rows: the rows of all fields of a lattice row are adjacent, so wide windows
+    // take them together
+    const bool all = g->L.interleaved && 4 * (size_t)w >= (size_t)g->L.pitch;
+    for (int q = 0; q < nf; q += all ? nf : 1) {
+      const char *src = (const char *)g->plane[g->parity][q] + ((size_t)y0 * g->L.rs + x0) * c;
+      const size_t span = all ? (size_t)(nf - 1) * g->L.pitch + w : w;
+      if ((e = fetch_window(stage, src, span, h, g->L.rs, c, &pitch)) != hipSuccess)
+        return hip_fail(e, "hipMemcpy D2H");
+      for (int k = q; k < (all ? nf : q + 1); ++k)
+        for (int y = 0; y < h; ++y) take(k, y, stage.data() + (size_t)y * pitch + (size_t)(k - q) * g->L.pitch * c);
+    }
+  } catch (...) {
+    return fail(LBT1_ENOMEM, "host staging");
+  }
+  return LBT1_OK;
+}
+
 // Decode the populations of rows y0..y0+h-1, columns x0..x0+w-1 of the current
 // parity into f[q][h][w] (deviations plus w_q).
 static lbt1_status read_pop_window(lbt1_grid *g, int x0, int y0, int w, int h, std::vector<double> &f) {
-  const size_t c = value_bytes(g->prec);
   const size_t n = (size_t)w * h;
-  std::vector<char> stage;
   try {
-    stage.resize(n * c);
     f.resize(9 * n);
   } catch (...) {
     return fail(LBT1_ENOMEM, "host staging");
   }
-  hipError_t e;
-  if ((e = hipSetDevice(g->device)) != hipSuccess) return hip_fail(e, "hipSetDevice");
-  if ((e = hipStreamSynchronize(g->stream)) != hipSuccess) return hip_fail(e, "hipStreamSynchronize");
-  for (int q = 0; q < 9; ++q) {
-    const char *src = (const char *)g->plane[g->parity][q] + ((size_t)y0 * g->L.rs + x0) * c;
-    if ((e = hipMemcpy2D(stage.data(), (size_t)w * c, src, (size_t)g->L.rs * c, (size_t)w * c, h,
-                         hipMemcpyDeviceToHost)) != hipSuccess)
-      return hip_fail(e, "hipMemcpy2D D2H");
-    double *dst = f.data() + (size_t)q * n;
-    decode_values(g->prec, stage.data(), n, g->sc[0], dst);
-    for (size_t i = 0; i < n; ++i) dst[i] += kHostW[q];
-  }
-  return LBT1_OK;
+  return read_fields(g, 9, x0, y0, w, h, [&](int q, int y, const char *row) {
+    double *dst = f.data() + (size_t)q * n + (size_t)y * w;
+    decode_values(g->prec, row, w, g->sc[0], dst);
+    for (int x = 0; x < w; ++x) dst[x] += kHostW[q];
+  });
 }
 
 }  // namespace lbt1
@@ -1120,10 +1187,8 @@ lbt1_status lbt1_set_geometry(lbt1_grid *g, const uint8_t *flags, const double *
   hipError_t e;
   if ((e = hipSetDevice(g->device)) != hipSuccess) return hip_fail(e, "hipSetDevice");
   if ((e = hipStreamSynchronize(g->stream)) != hipSuccess) return hip_fail(e, "hipStreamSynchronize");
-  for (int p = 0; p < 2; ++p)
-    if ((e = hipMemcpy(g->base + (size_t)p * g->L.state, stage.data(), g->L.state, hipMemcpyHostToDevice)) != hipSuccess)
-      return hip_fail(e, "hipMemcpy H2D");
-  if (g->snap[0] && (e = hipMemcpy(g->base + g->L.snap_off, stage.data(), g->L.state, hipMemcpyHostToDevice)) != hipSuccess)
+  if ((e = upload(g->base, stage.data(), g->L.state, {g->base + g->L.state, g->snap[0] ? g->base + g->L.snap_off : nullptr},
+                  g->stream)) != hipSuccess)
     return hip_fail(e, "hipMemcpy H2D");
   if ((e = hipMemcpy(g->flags, fstage.data(), plane_vals, hipMemcpyHostToDevice)) != hipSuccess)
     return hip_fail(e, "hipMemcpy H2D");
@@ -1189,28 +1254,14 @@ lbt1_status lbt1_read_window(lbt1_grid *g, int32_t x0, int32_t y0, int32_t w, in
     }
     return LBT1_OK;
   }
-  const size_t c = value_bytes(g->prec);
-  std::vector<char> stage;
-  try {
-    stage.resize(n * c);
-  } catch (...) {
-    return fail(LBT1_ENOMEM, "host staging");
-  }
-  hipError_t e;
-  if ((e = hipSetDevice(g->device)) != hipSuccess) return hip_fail(e, "hipSetDevice");
-  if ((e = hipStreamSynchronize(g->stream)) != hipSuccess) return hip_fail(e, "hipStreamSynchronize");
-  for (int q = 0; q < 3; ++q) {
+  return read_fields(g, 3, x0, y0, w, h, [&](int q, int y, const char *row) {
     double *dst = q == 0 ? rho : q == 1 ? jx : jy;
-    if (!dst) continue;
-    const char *src = (const char *)g->plane[g->parity][q] + ((size_t)y0 * g->L.rs + x0) * c;
-    if ((e = hipMemcpy2D(stage.data(), (size_t)w * c, src, (size_t)g->L.rs * c, (size_t)w * c, h,
-                         hipMemcpyDeviceToHost)) != hipSuccess)
-      return hip_fail(e, "hipMemcpy2D D2H");
-    decode_values(g->prec, stage.data(), n, g->sc[q == 0 ? 0 : 1], dst);
+    if (!dst) return;
+    dst += (size_t)y * w;
+    decode_values(g->prec, row, w, g->sc[q == 0 ? 0 : 1], dst);
     if (q == 0)
-      for (size_t i = 0; i < n; ++i) dst[i] += 1.0;
-  }
-  return LBT1_OK;
+      for (int x = 0; x < w; ++x) dst[x] += 1.0;
+  });
 }
 
 lbt1_status lbt1_read_moments(lbt1_grid *g, double *rho, double *jx, double *jy) {
@@ -1318,9 +1369,8 @@ lbt1_status lbt1_load_state(lbt1_grid *g, const void *host, size_t bytes) {
   if ((e = hipStreamSynchronize(g->stream)) != hipSuccess) return hip_fail(e, "hipStreamSynchronize");
   const char *h = (const char *)host;
   // both parities: non-FLUID nodes are read from either
-  for (int p = 0; p < 2; ++p)
-    if ((e = hipMemcpy(g->base + (size_t)p * g->L.state, h, g->L.state, hipMemcpyHostToDevice)) != hipSuccess)
-      return hip_fail(e, "hipMemcpy H2D");
+  if ((e = upload(g->base, h, g->L.state, {g->base + g->L.state}, g->stream)) != hipSuccess)
+    return hip_fail(e, "hipMemcpy H2D");
   if (snapshot_bytes(g) &&
       (e = hipMemcpy(g->base + g->L.snap_off, h + g->L.state, snapshot_bytes(g), hipMemcpyHostToDevice)) != hipSuccess)
     return hip_fail(e, "hipMemcpy H2D");

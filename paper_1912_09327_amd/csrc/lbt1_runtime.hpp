@@ -2,6 +2,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <initializer_list>
 #include <string>
 #include <vector>
 
@@ -37,6 +38,8 @@ lbt1_status check_device(int *dev_out, int *cus);
 void encode_values(int prec, const double *in, size_t n, double inv_scale, void *out);
 void decode_values(int prec, const void *in, size_t n, double scale, double *out);
 lbt1_status hip_fail(hipError_t e, const char *what);
+hipError_t upload(void *dst, const void *host, size_t bytes, std::initializer_list<void *> more, hipStream_t s);
+hipError_t fetch_window(std::vector<char> &stage, const void *src, size_t w, size_t h, size_t stride, size_t c, size_t *pitch);
 void clear_error();
 
 }  // namespace lbt1

@@ -272,10 +272,10 @@ typedef struct {
   /* STRIP with vec 32, 64 or 128: regions held in registers.  A block of `waves`
      wavefronts (8 or 16) holds a region of vec columns by `rows` rows (32 or 64) and
      takes `fuse` steps (1..64) per launch; the region's halo, that many nodes on each
-     side that is not a grid edge, must leave something to store.  Any width, any
-     geometry, any step count, no multiphase; the shapes built depend on the precision
-     and on walls (lbt1_set_kernel says EINVAL for others).  AUTO takes these except for
-     large grids in 16-bit storage. */
+     side that is not a grid edge (multiphase: twice as many), must leave something to
+     store.  Any width, any geometry, any step count; the shapes built depend on the
+     precision, on walls and on multiphase (lbt1_set_kernel says EINVAL for others).
+     AUTO takes these except for large grids in 16-bit storage. */
 } lbt1_kernel_config;
 
 /* Select the step kernel for a grid.  EINVAL if the combination is not built

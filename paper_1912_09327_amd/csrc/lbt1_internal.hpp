@@ -6,7 +6,7 @@
 
 namespace lbt1 {
 
-enum : int { KIND_GATHER = 1, KIND_STRIP = 2, KIND_BGK = 3, KIND_TILE = 4, KIND_BGK_TILE = 5 };
+enum : int { KIND_GATHER = 1, KIND_STRIP = 2, KIND_BGK = 3, KIND_TILE = 4, KIND_BGK_TILE = 5, KIND_SC_TILE = 6 };
 
 // One built step kernel.  Gather kernels take (StepArgs); strip kernels take
 // (StepArgs, StripMap); tile kernels take (StepArgs, TileMap); population (BGK)

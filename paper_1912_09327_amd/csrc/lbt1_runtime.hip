@@ -337,13 +337,13 @@ static bool is_tile(const lbt1_kernel_config &c) { return c.kernel == LBT1_KERNE
 
 
 // Tiles of configuration c on an nx x ny grid for a launch of `steps` steps: a halo
-// of that many nodes on each side of an axis, none on an axis that is not periodic and
+// of that many nodes (`reach` times as many) on each side of an axis, none on an axis that is not periodic and
 // fits the region whole.  False when the halo leaves nothing to store.
-bool tile_map(int nx, int ny, uint32_t periodic, const lbt1_kernel_config &c, int steps, TileMap *m) {
+bool tile_map(int nx, int ny, uint32_t periodic, const lbt1_kernel_config &c, int steps, TileMap *m, int reach) {
   m->steps = steps;
-  const int even = (steps + 1) / 2 * 2;  // chunks of two columns start at even columns
-  m->hx = !(periodic & 1u) && nx <= c.vec ? 0 : c.vec > 64 ? even : steps;
-  m->hy = !(periodic & 2u) && ny <= c.rows ? 0 : steps;
+  const int halo = steps * reach, even = (halo + 1) / 2 * 2;  // chunks of two columns start at even columns
+  m->hx = !(periodic & 1u) && nx <= c.vec ? 0 : c.vec > 64 ? even : halo;
+  m->hy = !(periodic & 2u) && ny <= c.rows ? 0 : halo;
   m->ox = c.vec - 2 * m->hx;
   m->oy = c.rows - 2 * m->hy;
   if (m->ox < 1 || m->oy < 1) return false;
@@ -352,12 +352,15 @@ bool tile_map(int nx, int ny, uint32_t periodic, const lbt1_kernel_config &c, in
   m->per_xcd = (m->tiles + 7) / 8;
   return true;
 }
-static bool is_tile_kind(const StepKernel *k) { return k->kind == KIND_TILE || k->kind == KIND_BGK_TILE; }
+static bool is_tile_kind(const StepKernel *k) { return k->kind >= KIND_TILE; }
+// nodes of a region's halo that a step of the kind uses up
+static int reach_of(int kind) { return kind == KIND_SC_TILE ? 2 : 1; }
 static dim3 tile_grid(const TileMap &m) { return dim3(8 * (unsigned)m.per_xcd, 1, 1); }
 
-// Steps of a launch the choice is made over (and the autotuner's candidates).  One step
-// of a launch widens the halo by a node; three and fewer measured slower on every grid.
-static const int kTileSteps[] = {4, 6, 8, 10, 12, 16, kMaxTileSteps};
+// Steps of a launch the choice is made over (and the autotuner's candidates).  Single-phase
+// grids take four or more (three and fewer measured slower on each); a multiphase step
+// uses up two nodes of the halo.
+static const int kTileSteps[] = {2, 3, 4, 6, 8, 10, 12, 16, kMaxTileSteps};
 
 // Modelled us per step of a tile kernel on `tiles` blocks: a launch takes us_launch and, for
 // each block that falls to the busiest CU (past eight rounds the average: blocks end at
@@ -382,6 +385,7 @@ static lbt1_kernel_config tile_choice(int kind, int prec, bool haswall, int wall
     const StepKernel &k = t[i];
     if (k.kind != kind || k.prec != prec || (k.haswall != 0) != haswall || (haswall && k.wall != wall)) continue;
     for (int steps : kTileSteps) {
+      if (steps < 4 && kind != KIND_SC_TILE) continue;
       lbt1_kernel_config c{};
       c.kernel = LBT1_KERNEL_STRIP;
       c.vec = k.vec;
@@ -389,7 +393,7 @@ static lbt1_kernel_config tile_choice(int kind, int prec, bool haswall, int wall
       c.waves = k.threads / 64;
       c.fuse = steps;
       TileMap m;
-      if (!tile_map(nx, ny, periodic, c, steps, &m)) continue;
+      if (!tile_map(nx, ny, periodic, c, steps, &m, reach_of(kind))) continue;
       const double us = tile_us(k, steps, m.tiles, cus);
       if (us < best_us) {
         best_us = us;
@@ -427,31 +431,23 @@ static lbt1_kernel_config default_config(int prec, bool haswall, int wall, int n
   return best;
 }
 
-// Default without a tuned entry for a multiphase grid: strips (2 columns per lane) on
-// periodic grids without walls that give every CU two strips or more, else one thread
-// per node.  FP32 grids with two 22-row strips of two fused steps per CU take those
-// (drop fields: 71.5 against 82.4 us per step at 4096^2, 232 against 284 at 8192^2).
-static lbt1_kernel_config sc_choice(int prec, bool haswall, int nx, int ny, int cus) {
-  lbt1_kernel_config c{};
-  c.kernel = LBT1_KERNEL_GATHER;
-  if ((long)nx * ny < 64 * 64) return c;
-  const long fused = (long)((nx / 4 + 61) / 62) * ((ny + 21) / 22);
-  if (prec == LBT1_F32 && !haswall && nx % 4 == 0 && fused >= 2L * cus &&
-      find_kernel(prec, false, 0, KIND_STRIP, 4, 22, 2, true)) {
-    c.kernel = LBT1_KERNEL_STRIP;
-    c.vec = 4;
-    c.rows = 22;
-    c.fuse = 2;
-    return c;
+// Default without a tuned entry for a multiphase grid: the tile kernel too (us per step on
+// drop fields, tile against the best of the strips: FP32 128^2 1.2 / 5.1, 1024^2 5.7 / 7.8,
+// 4096^2 54.7 / 67; FP64 1024^2 8.3 / 12.1, 4096^2 100 / 149; with walls, where only the
+// gather kernel applied, FP32 128^2 1.8 / 24.8, 1024^2 7.2 / 109).  16-bit storage on large
+// periodic grids takes one-step strips of 14 rows (FP16S 4096^2 50.5 against 55; 2048^2 19.4
+// against 17.1).
+static lbt1_kernel_config sc_choice(int prec, bool haswall, int wall, int nx, int ny, uint32_t periodic, int cus) {
+  double best_us;
+  lbt1_kernel_config best = tile_choice(KIND_SC_TILE, prec, haswall, wall, nx, ny, periodic, cus, &best_us);
+  if ((prec == LBT1_F16S || prec == LBT1_BF16S) && !haswall && nx % 2 == 0 && 2.85e-6 * nx * ny + 6.0 < best_us) {
+    best = lbt1_kernel_config{};
+    best.kernel = LBT1_KERNEL_STRIP;
+    best.vec = 2;
+    best.rows = 14;
+    best.fuse = 1;
   }
-  const long strips = (long)((nx / 2 + 61) / 62) * ((ny + 13) / 14);
-  if (!haswall && nx % 2 == 0 && strips >= 2L * cus && find_kernel(prec, false, 0, KIND_STRIP, 2, 14, 1, true)) {
-    c.kernel = LBT1_KERNEL_STRIP;
-    c.vec = 2;
-    c.rows = 14;
-    c.fuse = 1;
-  }
-  return c;
+  return best;
 }
 
 // Resolve a configuration into a kernel and launch shape for grid g.
@@ -496,7 +492,7 @@ lbt1_status bind_config(lbt1_grid *g, const lbt1_kernel_config &want, int cus) {
     // everything bind_config checks) yields to the heuristic rather than failing
     if (have && bind_config(g, tuned, cus) == LBT1_OK) return LBT1_OK;
     if (have) clear_error();
-    c = g->mp ? sc_choice(g->prec, g->haswall, g->nx, g->ny, cus)
+    c = g->mp ? sc_choice(g->prec, g->haswall, g->wall, g->nx, g->ny, g->periodic, cus)
               : default_config(g->prec, g->haswall, g->wall, g->nx, g->ny, g->periodic, cus);
   }
   const StepKernel *k = nullptr, *k1 = nullptr, *k2 = nullptr;
@@ -527,12 +523,12 @@ lbt1_status bind_config(lbt1_grid *g, const lbt1_kernel_config &want, int cus) {
     // the same strip shape where one is built
     if (c.fuse == 3) k2 = find_kernel(g->prec, g->haswall, g->wall, KIND_STRIP, c.vec, c.rows, 2, g->mp);
   } else if (is_tile(c)) {
-    if (g->mp) return fail(LBT1_EINVAL, "multiphase grids have no tile kernel");
+    const int kind = g->mp ? KIND_SC_TILE : KIND_TILE;
     if (c.fuse < 1 || c.fuse > kMaxTileSteps)
       return fail(LBT1_EINVAL, "tile kernel: fuse %d must be between 1 and %d", c.fuse, kMaxTileSteps);
-    k = k1 = find_tile(KIND_TILE, g->prec, g->haswall, g->wall, c.vec, c.rows, c.waves);
+    k = k1 = find_tile(kind, g->prec, g->haswall, g->wall, c.vec, c.rows, c.waves);
     TileMap m;
-    if (k && !tile_map(g->nx, g->ny, g->periodic, c, c.fuse, &m))
+    if (k && !tile_map(g->nx, g->ny, g->periodic, c, c.fuse, &m, reach_of(kind)))
       return fail(LBT1_EINVAL, "tile kernel: a halo of %d steps leaves nothing of a %d x %d region", c.fuse, c.vec, c.rows);
   } else {
     return fail(LBT1_EINVAL, "unknown kernel family %d", c.kernel);
@@ -543,8 +539,8 @@ lbt1_status bind_config(lbt1_grid *g, const lbt1_kernel_config &want, int cus) {
   g->kern1 = k1;
   g->kern2 = k2;
   g->cfg = c;
-  g->launch_steps = k->kind == KIND_TILE ? c.fuse : k->steps;
-  if (k->kind == KIND_TILE) {
+  g->launch_steps = is_tile_kind(k) ? c.fuse : k->steps;
+  if (is_tile_kind(k)) {
     g->block = dim3(k->threads, 1, 1);  // (its grid depends on the steps of a launch)
   } else if (k->kind == KIND_GATHER) {
     g->block = dim3(64, 4, 1);
@@ -645,7 +641,7 @@ hipError_t launch_step(lbt1_grid *g, const StepKernel *k, int src_parity, hipStr
   }
   if (is_tile_kind(k)) {
     TileMap t;
-    if (!tile_map(g->nx, g->ny, g->periodic, g->cfg, steps, &t)) return hipErrorInvalidValue;
+    if (!tile_map(g->nx, g->ny, g->periodic, g->cfg, steps, &t, reach_of(k->kind))) return hipErrorInvalidValue;
     StepArgs a{};
     BgkArgs b{};
     if (g->pop)
@@ -683,7 +679,7 @@ static lbt1_status build_burst(lbt1_grid *g, int p) {
   std::vector<BgkArgs> bargv(g->pop ? launches : 0);
   StripMap m = g->map;
   TileMap tm{};
-  if (is_tile_kind(g->kern) && !tile_map(g->nx, g->ny, g->periodic, g->cfg, g->launch_steps, &tm)) {
+  if (is_tile_kind(g->kern) && !tile_map(g->nx, g->ny, g->periodic, g->cfg, g->launch_steps, &tm, reach_of(g->kern->kind))) {
     hipGraphDestroy(graph);
     return fail(LBT1_EINVAL, "no tiles");
   }
@@ -1481,11 +1477,12 @@ lbt1_status lbt1_autotune(lbt1_grid *g, int32_t steps, int32_t reps, lbt1_kernel
           c.fuse = f;
           cands.push_back(c);
         }
-  if (!g->mp) {
+  {
+    const int kind = g->mp ? KIND_SC_TILE : KIND_TILE;
     int nk = 0;
     const StepKernel *tk = step_kernels(&nk);
     for (int i = 0; i < nk; ++i) {
-      if (tk[i].kind != KIND_TILE || tk[i].prec != g->prec || (tk[i].haswall != 0) != g->haswall ||
+      if (tk[i].kind != kind || tk[i].prec != g->prec || (tk[i].haswall != 0) != g->haswall ||
           (g->haswall && tk[i].wall != g->wall))
         continue;
       for (int f : kTileSteps) {
@@ -1496,7 +1493,7 @@ lbt1_status lbt1_autotune(lbt1_grid *g, int32_t steps, int32_t reps, lbt1_kernel
         c.rows = tk[i].rows;
         c.waves = tk[i].threads / 64;
         c.fuse = f;
-        if (tile_map(g->nx, g->ny, g->periodic, c, f, &m)) cands.push_back(c);
+        if (tile_map(g->nx, g->ny, g->periodic, c, f, &m, reach_of(kind))) cands.push_back(c);
       }
     }
   }

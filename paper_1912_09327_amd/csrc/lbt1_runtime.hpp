@@ -103,6 +103,6 @@ lbt1_status enqueue_reduce(lbt1_grid *g, uint32_t what, hipStream_t s);
 // shape, the tiles of a grid, the modelled time of a step
 constexpr int kMaxTileSteps = 64;
 const StepKernel *find_tile(int kind, int prec, bool haswall, int wall, int w, int rows, int waves);
-bool tile_map(int nx, int ny, uint32_t periodic, const lbt1_kernel_config &c, int steps, TileMap *m);
+bool tile_map(int nx, int ny, uint32_t periodic, const lbt1_kernel_config &c, int steps, TileMap *m, int reach = 1);
 double tile_us(const StepKernel &k, int steps, long tiles, int cus);
 }  // namespace lbt1

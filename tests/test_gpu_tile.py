@@ -113,8 +113,47 @@ def test_tile_refusals():
     h = Grid(64, 64, prec="f32", periodic=3, multiphase=(-5.5, 1.0))
     try:
         h.set_geometry(None)
-        with pytest.raises(C.Lbt1Error) as e:
-            h.set_kernel("strip", vec=32, rows=32, waves=16, fuse=4)
+        with pytest.raises(C.Lbt1Error) as e:                     # a halo of two nodes a step
+            h.set_kernel("strip", vec=32, rows=32, waves=8, fuse=8)
         assert e.value.status == C.EINVAL
+        h.set_kernel("strip", vec=32, rows=32, waves=8, fuse=7)
     finally:
         h.close()
+
+
+@pytest.mark.parametrize("prec", ["f64", "f32", "f16s", "bf16s"])
+@pytest.mark.parametrize("kind", ["periodic", "obstacles", "open", "open_x"])
+@pytest.mark.parametrize("wall", ["paper", "halfway"])
+def test_multiphase_tile_bitwise_equals_single_steps(prec, kind, wall):
+    """Every built shape against the gather kernel: drops over walls and grid edges, odd
+    sides, grids smaller than a region, several tiles, a storage scale other than one."""
+    from paper_1912_09327_amd import _capi as C
+    from paper_1912_09327_amd.grid import Grid
+    if kind == "periodic" and wall == "halfway":
+        pytest.skip("no walls")
+    for nx, ny in ((61, 31), (64, 32), (9, 5), (131, 77)):
+        flags, _, _, _, per = _case(kind, nx, ny, nx)
+        rng = np.random.default_rng(ny)
+        y, x = np.mgrid[0:ny, 0:nx]
+        rho = 0.11 + 1.1 * (1 - np.tanh((np.hypot(x - nx / 2, y - ny / 2) - min(nx, ny) / 4) / 2))
+        rho *= 1 + 0.01 * rng.standard_normal(rho.shape)
+        if flags is not None:
+            rho[flags == I.SOLID] = 0.6
+        jx, jy = (rho * 0.01 * rng.standard_normal(rho.shape) for _ in range(2))
+        g = Grid(nx, ny, prec=prec, wall=wall, periodic=per, force=(1e-5, -2e-6), multiphase=(-5.5, 1.0),
+                 scale=(0.125, 0.0625) if nx == 131 else (0.0, 0.0))
+        try:
+            g.set_geometry(flags, rho, jx, jy)
+            assert "k_sc_tile" in g.kernel()[1]
+            g.set_kernel("gather")
+            g.step(9)
+            base = g.read_moments()
+            for w, rows in ((32, 32), (64, 32)) + (((64, 64),) if kind == "periodic" else ()):
+                for steps in (1, 2, 5):
+                    g.set_kernel("strip", vec=w, rows=rows, waves=8, fuse=steps)
+                    g.set_geometry(flags, rho, jx, jy)
+                    g.step(9)
+                    for a, b in zip(base, g.read_moments()):
+                        assert np.array_equal(a, b, equal_nan=True), (nx, ny, w, rows, steps)
+        finally:
+            g.close()

@@ -10,10 +10,11 @@ import pytest
 SHAPES = [(1, 32, 32), (1, 64, 32), (1, 64, 64), (2, 128, 64)]
 
 
-def tile_map(nx, ny, per, w, rows, steps):
-    even = (steps + 1) // 2 * 2
-    hx = 0 if not per & 1 and nx <= w else even if w > 64 else steps
-    hy = 0 if not per & 2 and ny <= rows else steps
+def tile_map(nx, ny, per, w, rows, halo):
+    """halo: the steps of a launch, twice as many for multiphase grids."""
+    even = (halo + 1) // 2 * 2
+    hx = 0 if not per & 1 and nx <= w else even if w > 64 else halo
+    hy = 0 if not per & 2 and ny <= rows else halo
     return hx, hy, w - 2 * hx, rows - 2 * hy
 
 

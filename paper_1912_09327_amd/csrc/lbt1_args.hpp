@@ -14,14 +14,6 @@ struct StripMap {
   int persistent;          // 0: one block per unit; else grid-stride within the XCD range
 };
 
-// Tiles of k_step_tile and k_bgk_tile: steps this launch takes, halo and stored nodes of a
-// tile on each axis, tiles per row of tiles, in all and per XCD (8 * per_xcd blocks).
-struct TileMap {
-  int steps;
-  int hx, hy, ox, oy;
-  int tiles_x, tiles, per_xcd;
-};
-
 struct ReduceArgs {
   const void *cur[3];
   void *snap[3];

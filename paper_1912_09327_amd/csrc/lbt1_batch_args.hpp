@@ -1,7 +1,7 @@
 // Descriptors of the batched engine's grids and launches, shared by the host
 // code of lbt1_batch.hip and the batched kernels.
 #pragma once
-#include "lbt1_args.hpp"
+#include "lbt1_tile_args.hpp"
 
 namespace lbt1 {
 

@@ -8,7 +8,7 @@
 
 #include "../../include/lbt1.h"
 #include "lbt1_internal.hpp"
-#include "lbt1_args.hpp"
+#include "lbt1_tile_args.hpp"
 
 namespace lbt1 {
 

@@ -1,4 +1,4 @@
-// LBMTau1 step kernels for gfx950 (templates; instantiated in lbt1_step_kernels.hip).
+// LBMTau1 step kernels for gfx950 (templates; instantiated in lbt1_kernels.hip).
 //
 // Two kernel families compute the same update with the same operation order
 // (the per-source emission of lbt1_device.hpp and the per-target sums in

@@ -25,7 +25,7 @@
 // issue rate, against 34.2 with three-step strips, which wait for memory at two
 // wavefronts per SIMD).
 #pragma once
-#include "lbt1_args.hpp"
+#include "lbt1_tile_args.hpp"
 #include "lbt1_device.hpp"
 #include "lbt1_step.hpp"
 

@@ -11,6 +11,7 @@
 #include <cmath>
 #include <cstring>
 #include <new>
+#include <utility>
 #include <vector>
 
 #include "../../include/lbt1.h"
@@ -57,8 +58,6 @@ static bool valid3(int nx, int ny, int nz) {
   return nx >= 3 && ny >= 3 && nz >= 1 && nx <= 16384 && ny <= 16384 && nz <= 16384;
 }
 
-typedef void (*Step3Fn)(Step3Args);
-
 static const void *step3_kernel(int prec, int q, bool haswall, int wall) {
 #define K3(P, Q)                                                                                        \
   if (prec == P && q == Q) {                                                                            \
@@ -72,33 +71,82 @@ static const void *step3_kernel(int prec, int q, bool haswall, int wall) {
   return nullptr;
 }
 
-// Planes a tile block marches through: 32, but 16 for the periodic kernels with
-// 16-bit storage (at 512^3, D3Q19: FP32 126.9k against 123.7k MLUPS at 16;
-// FP16S 131.0k against 137.1k at 32).  The wall-aware kernels take 32 in every
-// storage (FP16S lid-driven box at 512^3: 80.7k against 76.5k MLUPS at 16, and
-// 96 VGPRs against 116).
-template <int P>
-constexpr int zchunk_of() {
-  return P == P_F16S || P == P_BF16S ? 16 : 32;
-}
-constexpr int kZChunkWall = 32;
-static int zchunk_for(int prec, bool haswall) {
-  return haswall ? kZChunkWall : prec == P_F16S || prec == P_BF16S ? 16 : 32;
-}
-constexpr int kTile3Y = 8;   // rows of a tile block (64 x 8 nodes, 512 threads)
+struct March3 {
+  const void *fn;
+  int rows, threads, per_cu;  // of a block; blocks a compute unit holds
+};
 
-static const void *tile3_kernel(int prec, int q, bool haswall, int wall) {
-#define T3(P, Q)                                                                                          \
-  if (prec == P && q == Q) {                                                                              \
-    if (!haswall && Q == 27) return (const void *)&k_step3_lane<P, Q, zchunk_of<P>(), kTile3Y>;          \
-    if (!haswall) return (const void *)&k_step3_tile<P, Q, zchunk_of<P>(), kTile3Y>;                     \
-    return wall == WALL_PAPER ? (const void *)&k_step3_tile<P, Q, kZChunkWall, kTile3Y, true, WALL_PAPER> \
-                              : (const void *)&k_step3_tile<P, Q, kZChunkWall, kTile3Y, true, WALL_HALFWAY>; \
+template <int P, int Q, bool HASWALL, int WALL, int GROUPS, int WAVES, bool FLAT = false>
+static March3 march3_of() {
+  constexpr int RPT = 2, waves = GROUPS + march3_sides(RPT, GROUPS);
+  return {(const void *)&k_step3_march<P, Q, HASWALL, WALL, RPT, GROUPS, WAVES, FLAT>, RPT * GROUPS, 64 * waves,
+          4 * WAVES / waves};
+}
+
+// Blocks of each storage, lattice and wall rule.  32- and 16-bit storage fits 128 registers, so
+// one block of 16 wavefronts (15 of two rows, one of halo columns) fills a compute unit: with
+// 7 + 1 wavefronts, two blocks a unit, 256^3 FP32 takes 142-155 us instead of 111, the box of
+// 200 x 180 x 150 55 instead of 48.  FP64 keeps twice the registers: 11 + 1 wavefronts (168
+// registers) where that does not spill, 7 + 1 (256) otherwise (224^3, half-way, D3Q19: 206 us
+// against 268 with 7 + 1; D3Q19 periodic at 128^3: 36.5 with 15 + 1 and six registers spilled,
+// 29.8 with 11 + 1).  LOW: small blocks for grids that do not fill the chip (below).  FLAT:
+// one plane (1024 x 1024 x 1: 9.9 us against 21 with the planes on both sides formed as well).
+enum March3Kind { MARCH_TALL, MARCH_LOW, MARCH_FLAT };
+template <int P, int Q, bool HASWALL, int WALL>
+static March3 march3_shape(March3Kind kind) {
+  constexpr bool f64 = P == P_F64;
+  if (kind == MARCH_FLAT) return march3_of<P, Q, HASWALL, WALL, 7, f64 ? 3 : 4, true>();
+  if constexpr (!f64) {
+    if (kind == MARCH_LOW) return march3_of<P, Q, HASWALL, WALL, 7, 4>();
+    return march3_of<P, Q, HASWALL, WALL, 15, 4>();
+  } else if constexpr (Q == 19) {
+    return march3_of<P, Q, HASWALL, WALL, 11, 3>();
+  } else {
+    return march3_of<P, Q, HASWALL, WALL, 7, 2>();
   }
-  T3(P_F64, 19) T3(P_F64, 27) T3(P_F32, 19) T3(P_F32, 27) T3(P_F16S, 19) T3(P_F16S, 27) T3(P_BF16S, 19)
-  T3(P_BF16S, 27)
-#undef T3
-  return nullptr;
+}
+
+static March3 march3_kernel(int prec, int q, bool haswall, int wall, March3Kind kind) {
+#define M3(P, Q)                                                                     \
+  if (prec == P && q == Q) {                                                         \
+    if (!haswall) return march3_shape<P, Q, false, 0>(kind);                         \
+    return wall == WALL_PAPER ? march3_shape<P, Q, true, WALL_PAPER>(kind)           \
+                              : march3_shape<P, Q, true, WALL_HALFWAY>(kind);        \
+  }
+  M3(P_F64, 19) M3(P_F64, 27) M3(P_F32, 19) M3(P_F32, 27) M3(P_F16S, 19) M3(P_F16S, 27) M3(P_BF16S, 19)
+  M3(P_BF16S, 27)
+#undef M3
+  return {};
+}
+
+// Tiles of a grid: rows evenly over the fewest tiles, and the planes a block marches through
+// so that the rounds of blocks times the planes each of them forms (two more than it writes)
+// are fewest; that product goes to *planes.  A chunk of 32 planes for every grid, as the
+// kernels before had it, left 256 compute units with 3 or 5 blocks for 64^3.
+//
+// past: stores carry the non-temporal hint where one parity alone fills the 256 MB of the last
+// cache level, so that nothing of a step would still be there for the next: 256^3 FP32 (268 MB)
+// 114.5 -> 111.3 us, 320^3 210 -> 204.  Below, the hint costs: 256^3 FP16S (134 MB) 82 -> 105,
+// the box of 200 x 180 x 150 FP32 (92 MB) 47 -> 58.
+static March3Map march3_map(int nx, int ny, int nz, const March3 &k, int cus, size_t state, long *planes) {
+  March3Map m{};
+  m.tiles_x = (nx + kMarch3X - 1) / kMarch3X;
+  m.tiles_y = (ny + k.rows - 3) / (k.rows - 2);
+  m.oy = (ny + m.tiles_y - 1) / m.tiles_y;
+  const long plane = (long)m.tiles_x * m.tiles_y, slots = (long)k.per_cu * cus;
+  *planes = -1;
+  for (int chunks = 1; chunks <= nz; ++chunks) {
+    const int zc = (nz + chunks - 1) / chunks;
+    const long cost = (plane * ((nz + zc - 1) / zc) + slots - 1) / slots * (zc + 2);
+    if (*planes < 0 || cost < *planes) {
+      *planes = cost;
+      m.zc = zc;
+    }
+  }
+  m.tiles = (int)(plane * ((nz + m.zc - 1) / m.zc));
+  m.per_xcd = (m.tiles + 7) / 8;
+  m.past = state >= ((size_t)256 << 20);
+  return m;
 }
 
 static const void *reduce3_kernel(int prec) {
@@ -133,22 +181,39 @@ struct lbt1_grid3d {
   int parity = 0;
   bool geometry = false, haswall = false;
   int want = LBT1_KERNEL_AUTO;  // kernel family asked for
-  bool tile = false;            // the z-marching LDS tile kernel is bound
+  bool tile = false;            // k_step3_march is bound
   const void *kern = nullptr;
+  March3Map map{};
+  dim3 grid, block;
+  int cus = 0;
 };
 
-// AUTO and STRIP take a tile kernel: on fully periodic grids without SOLID or
-// FIXED nodes k_step3_lane for D3Q27 (at 512^3, FP32: 112.2k against 107.6k
-// MLUPS for k_step3_tile) and k_step3_tile for D3Q19 (137.3k against 105.2k: its
-// 64-column tiles divide the power-of-two sides, while 62-column tiles leave
-// 12.5 % of the lanes idle at 512, and D3Q19 reads too little from LDS to gain
-// from the lane shifts); k_step3_tile's wall-aware form otherwise.  GATHER: the
-// one-thread-per-node kernel.
-static bool lane3(const lbt1_grid3d *g) { return g->tile && !g->haswall && g->q == 27; }
-
+// AUTO and STRIP take k_step3_march; GATHER: the one-thread-per-node kernel.  Low blocks are
+// taken where each has a compute unit to itself and forms no more planes than the tall one
+// would: 24^3 box 9.6 -> 7.6 us a step, 130 x 120 x 8 9.7 -> 8.1; with two blocks a unit they
+// gain nothing (64^3 D3Q27 9.9 against 10.1).
 static lbt1_status bind3(lbt1_grid3d *g) {
   g->tile = g->want != LBT1_KERNEL_GATHER;
-  g->kern = g->tile ? tile3_kernel(g->prec, g->q, g->haswall, g->wall) : step3_kernel(g->prec, g->q, g->haswall, g->wall);
+  if (g->tile) {
+    auto take = [&](March3Kind kind, long *planes) {
+      const March3 k = march3_kernel(g->prec, g->q, g->haswall, g->wall, kind);
+      return std::make_pair(k, march3_map(g->nx, g->ny, g->nz, k, g->cus, g->L.state, planes));
+    };
+    long tall = 0, low = 0;
+    auto k = take(g->nz == 1 ? MARCH_FLAT : MARCH_TALL, &tall);
+    if (g->nz > 1) {
+      const auto l = take(MARCH_LOW, &low);
+      if (l.first.rows < k.first.rows && l.second.tiles <= g->cus && low <= tall) k = l;
+    }
+    g->kern = k.first.fn;
+    g->map = k.second;
+    g->grid = dim3(8 * g->map.per_xcd, 1, 1);
+    g->block = dim3(k.first.threads, 1, 1);
+  } else {
+    g->kern = step3_kernel(g->prec, g->q, g->haswall, g->wall);
+    g->grid = dim3((g->nx + 63) / 64, (g->ny + 3) / 4, g->nz);
+    g->block = dim3(64, 4, 1);
+  }
   if (!g->kern) return fail(LBT1_EINVAL, "no built 3-D kernel");
   return LBT1_OK;
 }
@@ -210,6 +275,7 @@ lbt1_status lbt1_grid3d_create(const lbt1_grid3d_desc *d, lbt1_grid3d **out) {
   lbt1_grid3d *g = new (std::nothrow) lbt1_grid3d();
   if (!g) return fail(LBT1_ENOMEM, "host allocation");
   g->device = dev;
+  g->cus = cus;
   g->nx = d->nx;
   g->ny = d->ny;
   g->nz = d->nz;
@@ -355,17 +421,10 @@ lbt1_status lbt1_grid3d_step(lbt1_grid3d *g, int64_t n) {
   if (!g->geometry) return fail(LBT1_ESTATE, "step before set_geometry");
   hipError_t e;
   if ((e = hipSetDevice(g->device)) != hipSuccess) return hip_fail(e, "hipSetDevice");
-  const dim3 block = g->tile ? dim3(64 * kTile3Y, 1, 1) : dim3(64, 4, 1);
-  // tile kernel: one block per tile, rounded up to a multiple of the 8 XCDs (the
-  // kernel maps block b to a tile of XCD b % 8's contiguous range)
-  const int tw = lane3(g) ? kLane3X : kTile3X;  // target columns per tile
-  const long ntiles = (long)((g->nx + tw - 1) / tw) * ((g->ny + kTile3Y - 1) / kTile3Y) *
-                      ((g->nz + zchunk_for(g->prec, g->haswall) - 1) / zchunk_for(g->prec, g->haswall));
-  const dim3 grid = g->tile ? dim3((unsigned)((ntiles + 7) / 8 * 8), 1, 1) : dim3((g->nx + 63) / 64, (g->ny + 3) / 4, g->nz);
   for (int64_t s = 0; s < n; ++s) {
     Step3Args a = step3_args(g, g->parity);
-    void *args[] = {&a};
-    if ((e = hipLaunchKernel(g->kern, grid, block, args, 0, g->stream)) != hipSuccess)
+    void *args[] = {&a, &g->map};
+    if ((e = hipLaunchKernel(g->kern, g->grid, g->block, args, 0, g->stream)) != hipSuccess)
       return hip_fail(e, "3-D step launch");
     g->parity ^= 1;
   }

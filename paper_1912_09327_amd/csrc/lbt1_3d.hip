@@ -489,8 +489,9 @@ lbt1_status lbt1_grid3d_reduce(lbt1_grid3d *g, uint32_t what, double *out) {
   a.sc_j = g->sc[1];
   a.what = what;
   a.partials = g->partials;
-  const long n = (long)g->nx * g->ny * g->nz;
-  const int blocks = (int)std::min<long>(g->L.nparts, std::max<long>(1, (n + 1023) / 1024));
+  const long per = 16 / (long)value_bytes(g->prec);  // values a thread takes at a time
+  const long n = (g->nx + per - 1) / per * g->ny * g->nz;
+  const int blocks = (int)std::min<long>(g->L.nparts, (n + 255) / 256);
   void *args[] = {&a};
   if ((e = hipLaunchKernel(reduce3_kernel(g->prec), dim3(blocks), dim3(256), args, 0, g->stream)) != hipSuccess)
     return hip_fail(e, "reduce launch");

@@ -774,43 +774,77 @@ struct Reduce3Args {
   double *partials;  // 8 per block
 };
 
+template <typename S, int V>
+struct alignas(V * sizeof(S)) Run3 {
+  S v[V];
+};
+
 // out slots: 0 sum d, 1..3 sum j, 4 max residual, 5 non-finite, 6 FLUID count
+// Bound by HBM: with the residual the state and the snapshot are read and the snapshot is
+// written.  A thread takes 16 bytes of each field at a time and steps to its next run by adding
+// the grid's stride in rows and runs.  256^3 FP32 (805 MB): 143 us, 5.6 TB/s; a value at a
+// time, with two 64-bit divisions each, 205.  The box of 200 x 180 x 150: 67 -> 48.
 template <int P>
 __global__ void __launch_bounds__(256) k_reduce3_partial(Reduce3Args a) {
   using T = Traits<P>;
   using S = typename T::S;
+  constexpr int V = 16 / sizeof(S);
   double acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-  const long n = (long)a.nx * a.ny * a.nz;
   const bool want_res = a.what & 4u;
-  for (long k = (long)blockIdx.x * blockDim.x + threadIdx.x; k < n; k += (long)gridDim.x * blockDim.x) {
-    const int x = (int)(k % a.nx);
-    const long yz = k / a.nx;
-    const int y = (int)(yz % a.ny);
-    const int z = (int)(yz / a.ny);
-    if (a.flags && a.flags[(long)z * a.fzs + (long)y * a.pitch + x] != NODE_FLUID) continue;
-    const long i = (long)z * a.zs + (long)y * a.rs + x;
-    double v[4];
-    S r[4];
+  // rows are pitch values (a multiple of 64) apart in every field, so a row's last run
+  // stays inside it
+  const int runs = (a.nx + V - 1) / V;
+  const long rows = (long)a.ny * a.nz;
+  const int stride = gridDim.x * blockDim.x, first = blockIdx.x * blockDim.x + threadIdx.x;
+  int run = first % runs;
+  long row = first / runs;
+  while (row < rows) {
+    const int x = run * V;
+    const long i = row * a.rs + x;
+    Run3<S, V> r[4], s[4];
+    Run3<uint8_t, V> fl;
 #pragma unroll
-    for (int m = 0; m < 4; ++m) {
-      r[m] = static_cast<const S *>(a.cur[m])[i];
-      v[m] = (double)T::dec(r[m]) * (m == 0 ? a.sc_d : a.sc_j);
-    }
-    for (int m = 0; m < 4; ++m) acc[m] += v[m];
-    const bool fin = __builtin_isfinite(v[0]) && __builtin_isfinite(v[1]) && __builtin_isfinite(v[2]) &&
-                     __builtin_isfinite(v[3]);
-    acc[5] += fin ? 0.0 : 1.0;
-    acc[6] += 1.0;
+    for (int m = 0; m < 4; ++m) r[m] = *reinterpret_cast<const Run3<S, V> *>(static_cast<const S *>(a.cur[m]) + i);
+    if (a.flags) fl = *reinterpret_cast<const Run3<uint8_t, V> *>(a.flags + row * a.pitch + x);
     if (want_res) {
-      const double rho = 1.0 + v[0];
-      const double sr = 1.0 + (double)T::dec(static_cast<S *>(a.snap[0])[i]) * a.sc_d;
-      double res = 0.0;
-      for (int m = 1; m < 4; ++m) {
-        const double su = (double)T::dec(static_cast<S *>(a.snap[m])[i]) * a.sc_j / sr;
-        res = __builtin_fmax(res, __builtin_fabs(v[m] / rho - su));
+#pragma unroll
+      for (int m = 0; m < 4; ++m) s[m] = *reinterpret_cast<const Run3<S, V> *>(static_cast<const S *>(a.snap[m]) + i);
+    }
+#pragma unroll
+    for (int k = 0; k < V; ++k) {
+      if (x + k >= a.nx || (a.flags && fl.v[k] != NODE_FLUID)) continue;
+      double v[4];
+#pragma unroll
+      for (int m = 0; m < 4; ++m) v[m] = (double)T::dec(r[m].v[k]) * (m == 0 ? a.sc_d : a.sc_j);
+#pragma unroll
+      for (int m = 0; m < 4; ++m) acc[m] += v[m];
+      const bool fin = __builtin_isfinite(v[0]) && __builtin_isfinite(v[1]) && __builtin_isfinite(v[2]) &&
+                       __builtin_isfinite(v[3]);
+      acc[5] += fin ? 0.0 : 1.0;
+      acc[6] += 1.0;
+      if (want_res) {
+        const double rho = 1.0 + v[0];
+        const double sr = 1.0 + (double)T::dec(s[0].v[k]) * a.sc_d;
+        double res = 0.0;
+#pragma unroll
+        for (int m = 1; m < 4; ++m) {
+          const double su = (double)T::dec(s[m].v[k]) * a.sc_j / sr;
+          res = __builtin_fmax(res, __builtin_fabs(v[m] / rho - su));
+        }
+        acc[4] = __builtin_fmax(acc[4], res);
+#pragma unroll
+        for (int m = 0; m < 4; ++m) s[m].v[k] = r[m].v[k];
       }
-      acc[4] = __builtin_fmax(acc[4], res);
-      for (int m = 0; m < 4; ++m) static_cast<S *>(a.snap[m])[i] = r[m];
+    }
+    if (want_res) {
+#pragma unroll
+      for (int m = 0; m < 4; ++m) *reinterpret_cast<Run3<S, V> *>(static_cast<S *>(a.snap[m]) + i) = s[m];
+    }
+    run += stride % runs;
+    row += stride / runs;
+    if (run >= runs) {
+      run -= runs;
+      ++row;
     }
   }
 #pragma unroll

@@ -383,7 +383,7 @@ static lbt1_status build_graph(lbt1_batch *b, int K, int mask) {
   hipGraphNode_t partial;
   if (!st) {
     void *args[] = {&ra};
-    st = add(batch_reduce_kernel(b->prec), dim3(std::max(8, b->cus * 4)), dim3(256), args, last, nlast, &partial);
+    st = add(batch_reduce_kernel(b->prec), dim3(std::max(8, b->cus * 8)), dim3(256), args, last, nlast, &partial);
   }
   if (!st) {
     void *args[] = {&ra};

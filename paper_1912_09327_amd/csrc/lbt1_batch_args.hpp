@@ -61,8 +61,12 @@ struct BatchClassifyArgs {
 // snapshot refreshed): every resident grid is cut into chunks of
 // kBatchReduceChunk nodes, one block reduces one chunk into partials[item],
 // then the partials of each active grid are combined in item order into
-// out[slot * 6 + q].
-constexpr int kBatchReduceChunk = 16384;
+// out[slot * 6 + q].  A block walks its chunk 256 nodes at a time, bound by the
+// latency of its loads, so chunks are short enough for a few small grids to fill the
+// chip: 40 uneven FP16S cavities (3 million nodes) 63 us with chunks of 16384, which
+// leave a quarter of the chip without a block; 100 steps of them with one check took
+// 987 us then, 944 with 4096.
+constexpr int kBatchReduceChunk = 4096;
 struct BatchReduceArgs {
   const BatchGrid *grids;
   void *const *snaps;   // 3 per slot

@@ -150,14 +150,21 @@ __global__ void __launch_bounds__(256) k_reduce_batch(BatchReduceArgs b) {
     S *n1 = static_cast<S *>(b.snaps[slot * 3 + 1]);
     S *n2 = static_cast<S *>(b.snaps[slot * 3 + 2]);
     double acc[6] = {0, 0, 0, 0, 0, 0};
-    const long nn = (long)g.nx * g.ny;
+    // one division per thread and item; further nodes by adding the block's stride
+    const int nx = g.nx, sy = 256 / nx, sx = 256 - sy * nx;
     const long m0 = (long)item.y * kBatchReduceChunk;
-    const long m1 = min(nn, m0 + kBatchReduceChunk);
-    for (long m = m0 + threadIdx.x; m < m1; m += blockDim.x) {
-      const int y = (int)(m / g.nx);
-      const int x = (int)(m - (long)y * g.nx);
-      const long i = (long)y * g.rs + x;
-      if (g.flags[(long)y * g.pitch + x] != NODE_FLUID) continue;
+    const int count = (int)min((long)kBatchReduceChunk, (long)nx * g.ny - m0);
+    int y = (int)((m0 + threadIdx.x) / nx), x = (int)(m0 + threadIdx.x - (long)y * nx);
+    for (int k = threadIdx.x; k < count; k += 256) {
+      const int xn = x, yn = y;
+      x += sx;
+      y += sy;
+      if (x >= nx) {
+        x -= nx;
+        ++y;
+      }
+      const long i = (long)yn * g.rs + xn;
+      if (g.flags[(long)yn * g.pitch + xn] != NODE_FLUID) continue;
       const S r0 = c0[i], r1 = c1[i], r2 = c2[i];
       const double d = (double)T::dec(r0) * g.sc_d;
       const double jx = (double)T::dec(r1) * g.sc_j;

@@ -1,14 +1,16 @@
 // Batched stepping of many resident grids (lbt1_batch_* of include/lbt1.h).
 //
-// Every resident grid is cut into strips (62 chunks of vec columns by a class's
-// strip height) and belongs to one work class: one step per launch at 1, 2 or 4
-// columns per lane, or two steps per launch at 2 columns per lane (the fused
-// class, k_step_batch_fused).  The strips of all grids of a class form one work
+// Every resident grid belongs to one work class.  By default that is the tile class:
+// regions of nodes held in registers for several steps per launch.  A tile shape set
+// or tuned by the caller can cut grids into strips instead (62 chunks of vec columns
+// by a class's strip height): one step per launch at 1, 2 or 4 columns per lane, or
+// two steps per launch at 2 columns per lane (the fused class, k_step_batch_fused).
+// The regions or strips of all grids of a class form one work
 // list, and one launch per class and launch step covers the whole list, so a step
 // of hundreds of small, uneven grids costs a handful of launches.  Which class a
-// grid joins and each class's strip height are the batch's tile shape: a
-// heuristic by default (6-row strips for classes too short to give every CU
-// several wavefronts, since a strip walks its rows one after another), or what
+// grid joins and each class's strip height are the batch's tile shape (a height
+// left open: 6-row strips for classes too short to give every CU several wavefronts,
+// since a strip walks its rows one after another), or what
 // lbt1_batch_autotune measured fastest on the resident grids.  Each strip's kind
 // (interior, walls down whole columns, general), which picks the body it runs,
 // is found once per work list on the device (k_batch_classify) and kept in its

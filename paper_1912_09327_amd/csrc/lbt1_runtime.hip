@@ -409,7 +409,7 @@ static lbt1_kernel_config tile_choice(int kind, int prec, bool haswall, int wall
 //
 // In FP32 and FP64 that beat every strip and gather kernel at each size (us per step,
 // tile against the best of those: FP32 periodic 256^2 0.77 / 3.4, 1024^2 3.1 / 7.1,
-// 4096^2 29.0 / 31.1, 8192^2 107 / 108.5; FP32 cavity 256^2 1.02 / 2.85, 1024^2 4.6 /
+// 4096^2 29.0 / 31.1, 8192^2 107 / 108.5; FP32 cavity 256^2 0.91 / 2.85, 1024^2 4.6 /
 // 6.5, 8192^2 125 / 168; FP64 periodic 8192^2 224 / 302, cavity 274 / 540).  16-bit
 // storage pays its codec once per step either way, and the strips exchange columns off
 // the vector ALU: on large grids whose width they take, two-step strips of 14 rows are

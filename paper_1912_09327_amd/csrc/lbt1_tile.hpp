@@ -18,8 +18,8 @@
 // both parities and not written.  A region without walls takes a body that exchanges
 // reduced row sums; the choice is one vote per block and launch.
 //
-// Small grids are bound by the launch (256^2 FP32 cavity: 8.2 us for 8 steps, 3.3 us of
-// it arithmetic; 2.87 us per step before, 1.02 now), large ones by vector-ALU issue: the
+// Small grids are bound by the launch (256^2 FP32 cavity: 7.2 us for 8 steps, 4 us of it
+// the launch; 2.87 us per step before, 0.91 now), large ones by vector-ALU issue: the
 // wall-free step is 44 vector instructions a node, and a 128 x 64 region at 6 steps
 // stores 74 % of what it computes (4096^2 FP32: 28.8 us per step, about 94 % of the
 // issue rate, against 34.2 with three-step strips, which wait for memory at two

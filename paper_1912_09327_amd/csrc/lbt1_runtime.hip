@@ -754,8 +754,12 @@ lbt1_status enqueue_steps(lbt1_grid *g, int64_t n, hipStream_t s, bool use_graph
   }
   const int K = g->launch_steps;
   if (is_tile_kind(g->kern)) {
-    while (n > 0) {  // any number of steps up to K in a launch
-      const int k = (int)std::min<int64_t>(n, K);
+    // Any number of steps up to K in a launch: as few launches as K allows, with the steps
+    // spread over them.  A last launch of the few steps left over would move the state for
+    // them alone (8192^2 FP32, 99 steps and a reduction: 10.99 ms, 10.63 spread).
+    while (n > 0) {
+      const int64_t launches = (n + K - 1) / K;
+      const int k = (int)((n + launches - 1) / launches);
       if ((e = launch_step(g, g->kern, g->parity, s, k)) != hipSuccess) return hip_fail(e, "step launch");
       g->parity ^= 1;
       g->steps += k;

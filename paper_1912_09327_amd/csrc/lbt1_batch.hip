@@ -19,8 +19,8 @@
 // per class (the classes touch disjoint grids, so their chains run side by side);
 // the grid descriptors and work lists live in device memory, so admitting or
 // finishing grids changes data, not the graph (it is rebuilt only when the burst
-// length, the set of non-empty classes or a class's shape changes, or a list
-// outgrows its allocation).
+// length, the precision, the set of non-empty classes or a class's shape changes, or a
+// list outgrows its allocation).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -51,6 +51,21 @@ static const int kStepsOfClass[kStripClasses] = {1, 1, 1, 2, 0};  // 0: every st
 // and more, where two fused steps win).
 enum { FUSE_NONE = 0, FUSE_ALL = 1, FUSE_MIXED = 2 };
 constexpr int kMixedWide = 1024;
+
+// What a burst graph holds: its kernels and their launch sizes.  (The descriptors and the
+// lists they read are in device memory, see graph_valid.)
+struct GraphKey {
+  int steps = 0, mask = 0, prec = -1;
+  int rows[kClasses] = {}, blocks[kClasses] = {};
+  const BatchTileKernel *tile = nullptr;
+  int tile_steps = 0;
+  size_t lds_bytes = 0;
+  bool operator==(const GraphKey &o) const {
+    return steps == o.steps && mask == o.mask && prec == o.prec && std::equal(rows, rows + kClasses, o.rows) &&
+           std::equal(blocks, blocks + kClasses, o.blocks) && tile == o.tile && tile_steps == o.tile_steps &&
+           lds_bytes == o.lds_bytes;
+  }
+};
 
 struct Slot {
   lbt1_grid *g = nullptr;
@@ -108,8 +123,7 @@ struct lbt1_batch {
   int tile_steps = 8;
   bool items_dirty = true;
   hipGraphExec_t graph = nullptr;
-  int graph_K = 0, graph_mask = -1;
-  long graph_shape = -1;
+  lbt1::GraphKey graph_key;
   bool graph_valid = false;
 };
 
@@ -182,12 +196,19 @@ static int class_blocks(const lbt1_batch *b, int c) {
   return (int)std::max<long>(1, std::min<long>((long)per_cu * b->cus, need));
 }
 
-static long graph_shape(const lbt1_batch *b) {
-  long key = 0;
-  for (int c = 0; c < kClasses; ++c) key = key * 1000003L + b->rows[c] * 100003L + b->blocks[c];
-  key = key * 1000003L + b->tile_steps;
-  if (b->tile) key = key * 1000003L + b->tile->vec * 100L + b->tile->rows;
-  return key * 1000003L + (long)b->lds_bytes;
+// (the precision is part of it: an empty batch takes grids of another one, and grids of the
+// same sizes then have the same lists and launch sizes)
+static GraphKey graph_key(const lbt1_batch *b, int K, int mask) {
+  GraphKey k;
+  k.steps = K;
+  k.mask = mask;
+  k.prec = b->prec;
+  std::copy(b->rows, b->rows + kClasses, k.rows);
+  std::copy(b->blocks, b->blocks + kClasses, k.blocks);
+  k.tile = b->tile;
+  k.tile_steps = b->tile_steps;
+  k.lds_bytes = b->lds_bytes;
+  return k;
 }
 
 // Region shape and steps per launch of the tile class: the least modelled time of a step
@@ -401,9 +422,7 @@ static lbt1_status build_graph(lbt1_batch *b, int K, int mask) {
   e = hipGraphInstantiate(&b->graph, graph, nullptr, nullptr, 0);
   (void)hipGraphDestroy(graph);
   if (e != hipSuccess) return hip_fail(e, "hipGraphInstantiate");
-  b->graph_K = K;
-  b->graph_mask = mask;
-  b->graph_shape = graph_shape(b);
+  b->graph_key = graph_key(b, K, mask);
   b->graph_valid = true;
   return LBT1_OK;
 }
@@ -467,7 +486,7 @@ static lbt1_status launch_burst(lbt1_batch *b, int K, int *nact_out) {
         return hip_fail(e, "strip classification");
     }
   }
-  if (!b->graph_valid || b->graph_K != K || b->graph_mask != mask || b->graph_shape != graph_shape(b)) {
+  if (!b->graph_valid || !(b->graph_key == graph_key(b, K, mask))) {
     lbt1_status st = build_graph(b, K, mask);
     if (st) return st;
   }

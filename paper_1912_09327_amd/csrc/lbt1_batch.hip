@@ -221,6 +221,7 @@ static void choose_tile(lbt1_batch *b) {
       lbt1_kernel_config c{};
       c.vec = t->vec;
       c.rows = t->rows;
+      c.waves = t->threads / 64;
       long tiles = 0;
       bool ok = k != nullptr;
       for (const Slot &sl : b->slots) {
@@ -229,6 +230,9 @@ static void choose_tile(lbt1_batch *b) {
         ok = ok && tile_map(sl.g->nx, sl.g->ny, sl.g->periodic, c, steps, &m);
         if (ok) tiles += m.tiles;
       }
+      // (class_blocks rounds up by a quarter at most; regions of 64 x 64, or 64 x 32 in FP64, at
+      // 4 steps stay below 2^32 threads with every grid that 288 GB holds)
+      ok = ok && (tiles + tiles / 4 + 8) * t->threads < 1l << 32;
       const double us = ok ? tile_us(*k, steps, tiles, b->cus) : 1e300;
       if (us < best) {
         best = us;
@@ -279,6 +283,7 @@ static void rebuild_items(lbt1_batch *b) {
       lbt1_kernel_config c{};
       c.vec = b->tile->vec;
       c.rows = b->tile->rows;
+      c.waves = b->tile->threads / 64;
       (void)tile_map(sl.g->nx, sl.g->ny, sl.g->periodic, c, b->tile_steps, &m);
       BatchGrid &d = b->h_grids[s];
       d.strips_x = m.tiles_x;

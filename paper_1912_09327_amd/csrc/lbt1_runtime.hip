@@ -338,7 +338,9 @@ static bool is_tile(const lbt1_kernel_config &c) { return c.kernel == LBT1_KERNE
 
 // Tiles of configuration c on an nx x ny grid for a launch of `steps` steps: a halo
 // of that many nodes (`reach` times as many) on each side of an axis, none on an axis that is not periodic and
-// fits the region whole.  False when the halo leaves nothing to store.
+// fits the region whole.  False when the halo leaves nothing to store, or when the launch would
+// have 2^32 threads or more, which is past what a launch takes (the count wraps, without an
+// error, and most tiles are not run: 65536 x 4100 nodes in regions of 32 x 32 at 12 steps).
 bool tile_map(int nx, int ny, uint32_t periodic, const lbt1_kernel_config &c, int steps, TileMap *m, int reach) {
   m->steps = steps;
   const int halo = steps * reach, even = (halo + 1) / 2 * 2;  // chunks of two columns start at even columns
@@ -350,7 +352,7 @@ bool tile_map(int nx, int ny, uint32_t periodic, const lbt1_kernel_config &c, in
   m->tiles_x = (nx + m->ox - 1) / m->ox;
   m->tiles = m->tiles_x * ((ny + m->oy - 1) / m->oy);
   m->per_xcd = (m->tiles + 7) / 8;
-  return true;
+  return 8ll * m->per_xcd * 64 * c.waves < 1ll << 32;
 }
 static bool is_tile_kind(const StepKernel *k) { return k->kind >= KIND_TILE; }
 // nodes of a region's halo that a step of the kind uses up
@@ -529,7 +531,7 @@ lbt1_status bind_config(lbt1_grid *g, const lbt1_kernel_config &want, int cus) {
     k = k1 = find_tile(kind, g->prec, g->haswall, g->wall, c.vec, c.rows, c.waves);
     TileMap m;
     if (k && !tile_map(g->nx, g->ny, g->periodic, c, c.fuse, &m, reach_of(kind)))
-      return fail(LBT1_EINVAL, "tile kernel: a halo of %d steps leaves nothing of a %d x %d region", c.fuse, c.vec, c.rows);
+      return fail(LBT1_EINVAL, "tile kernel: a halo of %d steps leaves too little of a %d x %d region", c.fuse, c.vec, c.rows);
   } else {
     return fail(LBT1_EINVAL, "unknown kernel family %d", c.kernel);
   }

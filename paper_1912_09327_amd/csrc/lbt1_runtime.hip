@@ -156,8 +156,9 @@ static inline uint16_t encode_half(double v) {
   const uint16_t sign = (uint16_t)(uv >> 48) & 0x8000;
   const double a = std::fabs(r);
   const uint16_t normal = (uint16_t)((u >> 42) - (uint64_t)((1023 - 15) << 10)) & 0x7fff;
-  const uint16_t sub = (uint16_t)(int32_t)(a * 16777216.0);  // a < 2^-14: in units of 2^-24
-  uint16_t h = a < 6.103515625e-05 ? sub : normal;
+  constexpr double least = 6.103515625e-05;  // 2^-14
+  const uint16_t sub = (uint16_t)(int32_t)((a < least ? a : 0.0) * 16777216.0);  // in units of 2^-24
+  uint16_t h = a < least ? sub : normal;
   h = a > 65504.0 ? (uint16_t)0x7c00 : h;
   h = v != v ? (uint16_t)0x7e00 : h;
   return sign | h;
@@ -172,16 +173,16 @@ static inline uint16_t encode_bf16(double v) {
   const uint16_t sign = (uint16_t)(uv >> 48) & 0x8000;  // (a negative value that rounds to zero keeps it)
   return v != v ? (uint16_t)0x7fc0 : (uint16_t)((u >> 16 & 0x7fff) | sign);
 }
+// (no subnormal float on the way: a host thread may flush those to zero)
 static inline double decode_half(uint16_t b) {
-  // exponent and fraction as those of a float, scaled by 2^112; 31 becomes 255
-  const uint32_t e = (uint32_t)(b & 0x7fff) << 13;
-  float f;
-  std::memcpy(&f, &e, 4);
-  f *= 5.192296858534828e33f;  // 2^112
+  const uint32_t m = b & 0x7fff;
+  // normal: the exponent moved from bias 15 to 127; 31 becomes 255
+  const uint32_t normal = ((m << 13) + (112u << 23)) | (m >= 0x7c00 ? 0x7f800000u : 0u);
+  const float small = (float)(int32_t)m * 5.9604644775390625e-08f;  // m < 2^10: in units of 2^-24
   uint32_t u;
-  std::memcpy(&u, &f, 4);
-  u = (b & 0x7c00) == 0x7c00 ? (e | 0x7f800000u) : u;
-  u |= (uint32_t)(b & 0x8000) << 16;
+  std::memcpy(&u, &small, 4);
+  u = (m < 0x400 ? u : normal) | (uint32_t)(b & 0x8000) << 16;
+  float f;
   std::memcpy(&f, &u, 4);
   return (double)f;
 }

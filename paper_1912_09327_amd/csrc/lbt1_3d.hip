@@ -440,28 +440,23 @@ lbt1_status lbt1_grid3d_read_moments(lbt1_grid3d *g, double *rho, double *jx, do
   hipError_t e;
   if ((e = hipSetDevice(g->device)) != hipSuccess) return hip_fail(e, "hipSetDevice");
   if ((e = hipStreamSynchronize(g->stream)) != hipSuccess) return hip_fail(e, "hipStreamSynchronize");
-  double *dst[4] = {rho, jx, jy, jz};
-  try {
-    // plane by plane, all four fields: one copy of the plane's adjacent rows
-    std::vector<char> stage(((size_t)(ny - 1) * g->L.rs + 3 * (size_t)g->L.pitch + nx) * c);
-    for (int z = 0; z < nz; ++z) {
-      const char *src = (const char *)g->plane[g->parity][0] + (size_t)z * g->L.zs * c;
-      if ((e = hipMemcpy(stage.data(), src, stage.size(), hipMemcpyDeviceToHost)) != hipSuccess)
-        return hip_fail(e, "hipMemcpy D2H");
-      for (int y = 0; y < ny; ++y)
-        for (int m = 0; m < 4; ++m) {
-          if (!dst[m]) continue;
-          double *row = dst[m] + ((size_t)z * ny + y) * nx;
-          decode_values(g->prec, stage.data() + ((size_t)y * g->L.rs + (size_t)m * g->L.pitch) * c, nx,
-                        g->sc[m == 0 ? 0 : 1], row);
-          if (m == 0)
-            for (int x = 0; x < nx; ++x) row[x] += 1.0;
-        }
-    }
-  } catch (...) {
-    return fail(LBT1_ENOMEM, "host staging");
-  }
-  return LBT1_OK;
+  double *const dst[4] = {rho, jx, jy, jz};
+  const uint32_t fields = (rho ? 1u : 0u) | (jx ? 2u : 0u) | (jy ? 4u : 0u) | (jz ? 8u : 0u);
+  // the planes follow one another: ny * nz rows
+  RowSource s{};
+  s.src = (const char *)g->plane[g->parity][0];
+  s.c = c;
+  s.stride = (size_t)g->L.rs;
+  s.field = (size_t)g->L.pitch;
+  s.scratch = g->partials;
+  s.scratch_bytes = (size_t)g->L.nparts * 8 * sizeof(double);
+  s.stream = g->stream;
+  return read_rows(s, fields, nx, (size_t)ny * nz, [&](int m, size_t r, const char *row) {
+    double *out = dst[m] + r * nx;
+    decode_values(g->prec, row, nx, g->sc[m == 0 ? 0 : 1], out);
+    if (m == 0)
+      for (int x = 0; x < nx; ++x) out[x] += 1.0;
+  });
 }
 
 lbt1_status lbt1_grid3d_reduce(lbt1_grid3d *g, uint32_t what, double *out) {

@@ -253,21 +253,43 @@ hipError_t upload(void *dst, const void *host, size_t bytes, std::initializer_li
   return e == hipSuccess ? hipStreamSynchronize(s) : e;
 }
 
-// A window of `w` values by `h` rows (row stride `stride`, value size c) into `stage`, and the
-// position of row r in it, r * *pitch.  A strided copy goes row by row at about 20 us each
-// (701 rows: 15 ms); whole rows go as one copy, at 8 GB/s or more, so they do unless the window
-// is much narrower than its rows.
-hipError_t fetch_window(std::vector<char> &stage, const void *src, size_t w, size_t h, size_t stride, size_t c,
-                        size_t *pitch) {
-  const size_t whole = ((h - 1) * stride + w) * c;
-  if (h > 1 && whole < h * 160000) {
-    stage.resize(whole);
-    *pitch = stride * c;
-    return hipMemcpy(stage.data(), src, whole, hipMemcpyDeviceToHost);
+// Windows too narrow for whole rows, [field][row][w] (read_rows; the copy to the host bounds it)
+struct PackArgs {
+  const void *src;
+  void *dst;
+  unsigned long long stride, field;
+  unsigned int w, rows, n;
+  unsigned int which;  // bit q: field q is wanted
+};
+template <typename S>
+__global__ void __launch_bounds__(256) k_pack_rows(PackArgs a) {
+  const unsigned int total = a.n * a.rows * a.w;
+  for (unsigned int i = blockIdx.x * 256 + threadIdx.x; i < total; i += gridDim.x * 256) {
+    const unsigned int x = i % a.w, kr = i / a.w, r = kr % a.rows;
+    unsigned int which = a.which;
+    for (unsigned int k = kr / a.rows; k > 0; --k) which &= which - 1;
+    const unsigned int q = __builtin_ctz(which);
+    static_cast<S *>(a.dst)[i] = static_cast<const S *>(a.src)[r * a.stride + q * a.field + x];
   }
-  stage.resize(w * h * c);
-  *pitch = w * c;
-  return hipMemcpy2D(stage.data(), w * c, src, stride * c, w * c, h, hipMemcpyDeviceToHost);
+}
+
+// Rows row0 ... row0 + rows - 1 of the fields into the scratch, which holds them.
+hipError_t pack_rows(const RowSource &s, size_t row0, size_t rows, size_t w, uint32_t fields) {
+  PackArgs a{};
+  a.src = s.src + row0 * s.stride * s.c;
+  a.dst = s.scratch;
+  a.stride = s.stride;
+  a.field = s.field;
+  a.w = (unsigned int)w;
+  a.rows = (unsigned int)rows;
+  a.n = (unsigned int)__builtin_popcount(fields);
+  a.which = fields;
+  const void *fn = s.c == 8   ? (const void *)&k_pack_rows<uint64_t>
+                   : s.c == 4 ? (const void *)&k_pack_rows<uint32_t>
+                              : (const void *)&k_pack_rows<uint16_t>;
+  void *args[] = {&a};
+  const size_t total = a.n * rows * w;
+  return hipLaunchKernel(fn, dim3((unsigned int)std::min<size_t>(96, (total + 255) / 256)), dim3(256), args, 0, s.stream);
 }
 
 // ----------------------------------------------------------------- device check
@@ -967,32 +989,23 @@ static lbt1_status set_geometry_pop(lbt1_grid *g, const uint8_t *flags, const do
   return LBT1_OK;
 }
 
-// The stored values of fields 0 .. nf - 1 of the current parity in rows y0 .. y0+h-1,
-// columns x0 .. x0+w-1: take(q, y, row) for each field and row, once the stream is done.
+// The stored values of the fields (bits) of the current parity in rows y0 .. y0+h-1, columns
+// x0 .. x0+w-1: take(q, y, row) for each field and row, once the stream is done.
 template <typename F>
-static lbt1_status read_fields(lbt1_grid *g, int nf, int x0, int y0, int w, int h, const F &take) {
+static lbt1_status read_fields(lbt1_grid *g, uint32_t fields, int x0, int y0, int w, int h, const F &take) {
   const size_t c = value_bytes(g->prec);
   hipError_t e;
   if ((e = hipSetDevice(g->device)) != hipSuccess) return hip_fail(e, "hipSetDevice");
   if ((e = hipStreamSynchronize(g->stream)) != hipSuccess) return hip_fail(e, "hipStreamSynchronize");
-  try {
-    std::vector<char> stage;
-    size_t pitch = 0;
-    // interleaved rows: the rows of all fields of a lattice row are adjacent, so wide windows
-    // take them together
-    const bool all = g->L.interleaved && 4 * (size_t)w >= (size_t)g->L.pitch;
-    for (int q = 0; q < nf; q += all ? nf : 1) {
-      const char *src = (const char *)g->plane[g->parity][q] + ((size_t)y0 * g->L.rs + x0) * c;
-      const size_t span = all ? (size_t)(nf - 1) * g->L.pitch + w : w;
-      if ((e = fetch_window(stage, src, span, h, g->L.rs, c, &pitch)) != hipSuccess)
-        return hip_fail(e, "hipMemcpy D2H");
-      for (int k = q; k < (all ? nf : q + 1); ++k)
-        for (int y = 0; y < h; ++y) take(k, y, stage.data() + (size_t)y * pitch + (size_t)(k - q) * g->L.pitch * c);
-    }
-  } catch (...) {
-    return fail(LBT1_ENOMEM, "host staging");
-  }
-  return LBT1_OK;
+  RowSource s{};
+  s.src = (const char *)g->plane[g->parity][0] + ((size_t)y0 * g->L.rs + x0) * c;
+  s.c = c;
+  s.stride = g->L.rs;
+  s.field = (g->L.field_off[1] - g->L.field_off[0]) / c;
+  s.scratch = g->partials;
+  s.scratch_bytes = (size_t)g->L.nparts * 6 * sizeof(double);
+  s.stream = g->stream;
+  return read_rows(s, fields, w, h, take);
 }
 
 // Decode the populations of rows y0..y0+h-1, columns x0..x0+w-1 of the current
@@ -1004,8 +1017,8 @@ static lbt1_status read_pop_window(lbt1_grid *g, int x0, int y0, int w, int h, s
   } catch (...) {
     return fail(LBT1_ENOMEM, "host staging");
   }
-  return read_fields(g, 9, x0, y0, w, h, [&](int q, int y, const char *row) {
-    double *dst = f.data() + (size_t)q * n + (size_t)y * w;
+  return read_fields(g, 0x1ffu, x0, y0, w, h, [&](int q, size_t y, const char *row) {
+    double *dst = f.data() + (size_t)q * n + y * w;
     decode_values(g->prec, row, w, g->sc[0], dst);
     for (int x = 0; x < w; ++x) dst[x] += kHostW[q];
   });
@@ -1257,10 +1270,10 @@ lbt1_status lbt1_read_window(lbt1_grid *g, int32_t x0, int32_t y0, int32_t w, in
     }
     return LBT1_OK;
   }
-  return read_fields(g, 3, x0, y0, w, h, [&](int q, int y, const char *row) {
-    double *dst = q == 0 ? rho : q == 1 ? jx : jy;
-    if (!dst) return;
-    dst += (size_t)y * w;
+  double *const dsts[3] = {rho, jx, jy};
+  const uint32_t fields = (rho ? 1u : 0u) | (jx ? 2u : 0u) | (jy ? 4u : 0u);
+  return read_fields(g, fields, x0, y0, w, h, [&](int q, size_t y, const char *row) {
+    double *dst = dsts[q] + y * w;
     decode_values(g->prec, row, w, g->sc[q == 0 ? 0 : 1], dst);
     if (q == 0)
       for (int x = 0; x < w; ++x) dst[x] += 1.0;

@@ -2,7 +2,10 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <initializer_list>
+#include <memory>
+#include <new>
 #include <string>
 #include <vector>
 
@@ -38,9 +41,77 @@ lbt1_status check_device(int *dev_out, int *cus);
 void encode_values(int prec, const double *in, size_t n, double inv_scale, void *out);
 void decode_values(int prec, const void *in, size_t n, double scale, double *out);
 lbt1_status hip_fail(hipError_t e, const char *what);
-hipError_t upload(void *dst, const void *host, size_t bytes, std::initializer_list<void *> more, hipStream_t s);
-hipError_t fetch_window(std::vector<char> &stage, const void *src, size_t w, size_t h, size_t stride, size_t c, size_t *pitch);
 void clear_error();
+hipError_t upload(void *dst, const void *host, size_t bytes, std::initializer_list<void *> more, hipStream_t s);
+
+// Rows of stored values in device memory: row r of field q starts r * stride + q * field values
+// of c bytes after src.  scratch: device memory of the grid that a readout may overwrite.
+struct RowSource {
+  const char *src;
+  size_t c, stride, field;
+  void *scratch;
+  size_t scratch_bytes;
+  hipStream_t stream;
+};
+hipError_t pack_rows(const RowSource &s, size_t row0, size_t rows, size_t w, uint32_t fields);
+
+// take(q, r, row) with the w stored values of row r of each field q of the bits `fields`.  One of
+// three ways, by an estimate of its time (measured: 8 bytes a nanosecond, 10 us a copy, and as
+// much for each row of a strided copy, 22 us for a launch that packs and its copy):
+//   whole rows of all the fields between, kReadStage bytes at a time, which the conversion then
+//   finds in the cache (8192^2 FP32: 92 ms, in one piece 255; box of 200 x 180 x 150: 10 ms);
+//   rows one by one, a strided copy, where rows are long and most of the fields are not wanted;
+//   packed on the device into `scratch` first, where the window is narrow: a column of an
+//   8192^2 FP32 grid in 0.1 ms, where whole rows move and stage 805 MB in 280 ms.
+constexpr size_t kReadStage = 1u << 20;
+template <typename F>
+lbt1_status read_rows(const RowSource &s, uint32_t fields, size_t w, size_t rows, const F &take) {
+  if (!fields) return LBT1_OK;
+  int q[32], n_ = 0;
+  for (int k = 0; k < 32; ++k)
+    if (fields >> k & 1u) q[n_++] = k;
+  const size_t n = (size_t)n_, first = (size_t)q[0], line = w * s.c;
+  const bool adjacent = s.field < s.stride;  // the rows of all fields of a lattice row
+  const size_t span = adjacent ? ((size_t)q[n - 1] - first) * s.field + w : w, passes = adjacent ? 1 : n;
+  const size_t fit = s.scratch_bytes / (n * line);  // rows of a launch that packs
+  const size_t wanted = n * rows * line, all = passes * ((rows - 1) * s.stride + span) * s.c;
+  const double whole = (passes + (double)all / kReadStage) * 1e4 + all / 8.0;
+  const double strided = n * rows * 1e4 + wanted / 8.0;
+  const double packed = fit ? ((rows + fit - 1) / fit) * 2.2e4 + wanted / 8.0 : 1e300;
+  enum { WHOLE, STRIDED, PACKED } how = packed < whole && packed < strided ? PACKED : strided < whole ? STRIDED : WHOLE;
+  const size_t few = how == PACKED    ? fit
+                     : how == STRIDED ? kReadStage / line
+                                      : kReadStage / (s.stride * s.c);
+  const size_t block = std::min(rows, std::max<size_t>(1, few));  // rows at a time
+  const size_t bytes = how == PACKED ? block * n * line : how == STRIDED ? block * line : ((block - 1) * s.stride + span) * s.c;
+  const std::unique_ptr<char[]> stage(new (std::nothrow) char[bytes]);
+  if (!stage) return fail(LBT1_ENOMEM, "host staging");
+  hipError_t e = hipSuccess;
+  const size_t turns = how == STRIDED ? n : how == WHOLE ? passes : 1;
+  for (size_t t = 0; t < turns; ++t)
+    for (size_t r = 0; r < rows; r += block) {
+      const size_t h = std::min(block, rows - r), from = how == WHOLE && adjacent ? first : (size_t)q[t];
+      const char *const src = s.src + (r * s.stride + from * s.field) * s.c;
+      if (how == PACKED) {
+        if ((e = pack_rows(s, r, h, w, fields)) == hipSuccess)
+          e = hipMemcpyAsync(stage.get(), s.scratch, h * n * line, hipMemcpyDeviceToHost, s.stream);
+        if (e == hipSuccess) e = hipStreamSynchronize(s.stream);
+      } else if (how == STRIDED) {
+        e = hipMemcpy2D(stage.get(), line, src, s.stride * s.c, line, h, hipMemcpyDeviceToHost);
+      } else {
+        e = hipMemcpy(stage.get(), src, ((h - 1) * s.stride + span) * s.c, hipMemcpyDeviceToHost);
+      }
+      if (e != hipSuccess) return hip_fail(e, "copy to the host");
+      const size_t k1 = how == PACKED || (how == WHOLE && adjacent) ? n : t + 1;
+      for (size_t y = 0; y < h; ++y)
+        for (size_t k = t; k < k1; ++k)
+          take(q[k], r + y,
+               stage.get() + (how == PACKED    ? (k * h + y) * line
+                              : how == STRIDED ? y * line
+                                               : (y * s.stride + ((size_t)q[k] - from) * s.field) * s.c));
+    }
+  return LBT1_OK;
+}
 
 }  // namespace lbt1
 

@@ -166,7 +166,11 @@ lbt1_status lbt1_set_geometry(lbt1_grid *g, const uint8_t *flags, const double *
                               const double *jx, const double *jy);
 
 /* Enqueue n >= 0 LBMTau1 steps (Algorithm 1) on the grid's stream and return.
- * ESTATE before lbt1_set_geometry. */
+ * ESTATE before lbt1_set_geometry.  A grid's state alternates between two
+ * parities, one launch after the other, so a call that a caller records into a
+ * graph of its own can be replayed where it takes an even number of launches:
+ * with the region kernels that AUTO takes (lbt1_kernel_config) every n >= 2 does,
+ * with the one-step kernels every even n. */
 lbt1_status lbt1_step(lbt1_grid *g, int64_t n);
 
 /* Copy the current density rho and momentum (jx, jy) into ny*nx host arrays

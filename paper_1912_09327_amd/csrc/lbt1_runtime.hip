@@ -760,7 +760,15 @@ static void drop_bursts(lbt1_grid *g) {
 lbt1_status enqueue_steps(lbt1_grid *g, int64_t n, hipStream_t s, bool use_graph) {
   hipError_t e;
   const int bs = burst_steps(g);
-  if (use_graph && n >= kBurst) {
+  // Recorded by a caller into a graph, tile launches are plain ones and even in number where
+  // there are two steps or more: every replay then reads the parity that the one before it
+  // wrote, as it does with single-step launches of an even number of steps.
+  bool recorded = false;
+  if (is_tile_kind(g->kern)) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    recorded = hipStreamIsCapturing(s, &st) == hipSuccess && st == hipStreamCaptureStatusActive;
+  }
+  if (use_graph && n >= kBurst && !recorded) {
     if (!g->graph_valid) {
       drop_bursts(g);
       g->graph_valid = true;
@@ -782,8 +790,9 @@ lbt1_status enqueue_steps(lbt1_grid *g, int64_t n, hipStream_t s, bool use_graph
     // Any number of steps up to K in a launch: as few launches as K allows, with the steps
     // spread over them.  A last launch of the few steps left over would move the state for
     // them alone (8192^2 FP32, 99 steps and a reduction: 10.99 ms, 10.63 spread).
-    while (n > 0) {
-      const int64_t launches = (n + K - 1) / K;
+    int64_t launches = (n + K - 1) / K;
+    if (recorded && n > 1) launches += launches & 1;
+    for (; n > 0; --launches) {
       const int k = (int)((n + launches - 1) / launches);
       if ((e = launch_step(g, g->kern, g->parity, s, k)) != hipSuccess) return hip_fail(e, "step launch");
       g->parity ^= 1;

@@ -4,8 +4,9 @@
 //
 // Every node keeps its nine populations as deviations g_q = f_q - w_q in the
 // storage format of the grid.  Single-phase grids take several steps per launch
-// (lbt1_bgk_tile.hpp); multiphase ones, whose force needs the pseudopotential of the
-// neighbours, one: a pass that writes psi, then one thread per node (push form):
+// (lbt1_bgk_tile.hpp) except where a call asks for one or two; those, and multiphase
+// grids, whose force needs the pseudopotential of the neighbours (a pass that writes psi
+// before each step), take one step with a thread per node (push form):
 // load the node's own nine populations, form rho - 1 and j, relax toward the
 // equilibrium of (rho, (j + tau F) / rho) with rate 1 / tau, and send each
 // relaxed population to the neighbour it points at.  A population that would
@@ -55,7 +56,7 @@ __global__ void __launch_bounds__(256) k_bgk_psi(BgkArgs a) {
       sc_psi<C>(C(1) + pop_density<C>(g), C(a.sc_rho0), C(1.0 / a.sc_rho0));
 }
 
-template <int P, bool HASWALL, int WALL>
+template <int P, bool HASWALL, int WALL, bool SC>
 __global__ void __launch_bounds__(256) k_bgk_step(BgkArgs a) {
   using T = Traits<P>;
   using C = typename T::C;
@@ -85,19 +86,22 @@ __global__ void __launch_bounds__(256) k_bgk_step(BgkArgs a) {
   const C jy = ((g[2] - g[4]) + (g[5] - g[7])) + (g[6] - g[8]);
   C post[9];
   if (!HASWALL || fl == NODE_FLUID) {
-    const C *ps = static_cast<const C *>(a.psi);
-    C psi[9];
-    psi[0] = ps[(long)y * a.pitch + x];
+    C Fx = C(a.fx), Fy = C(a.fy);
+    if (SC) {
+      const C *ps = static_cast<const C *>(a.psi);
+      C psi[9];
+      psi[0] = ps[(long)y * a.pitch + x];
 #pragma unroll
-    for (int k = 1; k < 9; ++k) {
-      const int tx = wrap_axis(x + kEx[k], a.nx, a.periodic & 1u);
-      const int ty = wrap_axis(y + kEy[k], a.ny, a.periodic & 2u);
-      psi[k] = (tx < 0 || ty < 0) ? psi[0] : ps[(long)ty * a.pitch + tx];
+      for (int k = 1; k < 9; ++k) {
+        const int tx = wrap_axis(x + kEx[k], a.nx, a.periodic & 1u);
+        const int ty = wrap_axis(y + kEy[k], a.ny, a.periodic & 2u);
+        psi[k] = (tx < 0 || ty < 0) ? psi[0] : ps[(long)ty * a.pitch + tx];
+      }
+      C gx, gy;
+      sc_force<C>(psi, C(a.sc_G), gx, gy);
+      Fx = C(a.tau) * (C(a.bfx) + gx);
+      Fy = C(a.tau) * (C(a.bfy) + gy);
     }
-    C gx, gy;
-    sc_force<C>(psi, C(a.sc_G), gx, gy);
-    const C Fx = C(a.tau) * (C(a.bfx) + gx);
-    const C Fy = C(a.tau) * (C(a.bfy) + gy);
     C geq[9];
     emit<C>(d, jx, jy, Fx, Fy, geq);
     const C om = C(a.omega);

@@ -475,8 +475,40 @@ static lbt1_kernel_config sc_choice(int prec, bool haswall, int wall, int nx, in
   return best;
 }
 
+// The launch shape of a thread per node on population grids.
+static dim3 push_grid(const lbt1_grid *g) {
+  const int tiles = ((g->nx + 63) / 64) * ((g->ny + 3) / 4);
+  return dim3((tiles + 7) / 8 * 8, 1, 1);
+}
+
+// Calls of one or two steps on population grids: k_bgk_step, a launch a step, where the tile
+// kernel takes longer for so few (us of a call, k_bgk_step / k_bgk_tile: periodic FP32 64^2 one
+// step 3.3 / 4.8, 512^2 one 4.4 / 9.2, two 9.0 / 11.3, three 13.3 / 13.0; 2048^2 one 55 / 70, two
+// 110 / 68; FP64 cavity 384^2 one 7.5 / 11.0, two 14 / 12.5).  Periodic grids take it for every
+// single step; otherwise its time is modelled as a launch and the bytes at the rate of the last
+// cache level, lower with walls, whose flags are read for each neighbour, and two launches are
+// not worth it on the smallest grids (FP64 64^2: 7.5 / 6.0).
+static void brief_populations(lbt1_grid *g, int cus) {
+  const double nodes = (double)g->nx * g->ny, bytes = nodes * 18 * value_bytes(g->prec);
+  const double push = g->haswall ? 5.0 + (bytes + nodes) / 5e6 : 3.0 + bytes / 7e6;
+  const dim3 grid = push_grid(g);
+  if ((double)grid.x * 256 >= 4294967296.0) return;  // past what a launch takes
+  for (int n = 1; n <= kBrief; ++n) {
+    TileMap m;
+    if (!tile_map(g->nx, g->ny, g->periodic, g->cfg, n, &m)) continue;
+    const bool less = push < tile_us(*g->kern, n, m.tiles, cus) && (n == 1 || nodes >= 2e5);
+    if (!less && (n > 1 || g->haswall)) continue;
+    Brief &b = g->brief[n - 1];
+    b.kern = find_kernel(g->prec, g->haswall, g->wall, KIND_BGK, 0, 0, 1, false);
+    b.times = n;
+    b.grid = grid;
+    b.block = dim3(256, 1, 1);
+  }
+}
+
 // Resolve a configuration into a kernel and launch shape for grid g.
 lbt1_status bind_config(lbt1_grid *g, const lbt1_kernel_config &want, int cus) {
+  for (Brief &b : g->brief) b = Brief{};
   if (g->pop) {
     g->kern2 = nullptr;
     g->graph_valid = false;
@@ -489,6 +521,7 @@ lbt1_status bind_config(lbt1_grid *g, const lbt1_kernel_config &want, int cus) {
       g->kern = g->kern1 = k;
       g->launch_steps = g->cfg.fuse;
       g->block = g->block1 = dim3(k->threads, 1, 1);
+      brief_populations(g, cus);
       return LBT1_OK;
     }
     // multiphase: one step at a time, a thread per node (the gather launch shape)
@@ -499,9 +532,8 @@ lbt1_status bind_config(lbt1_grid *g, const lbt1_kernel_config &want, int cus) {
     g->cfg = lbt1_kernel_config{};
     g->cfg.kernel = LBT1_KERNEL_GATHER;
     g->cfg.fuse = 1;
-    const int tiles = ((g->nx + 63) / 64) * ((g->ny + 3) / 4);
     g->block = g->block1 = dim3(256, 1, 1);
-    g->grid = g->grid1 = dim3((tiles + 7) / 8 * 8, 1, 1);
+    g->grid = g->grid1 = push_grid(g);
     return LBT1_OK;
   }
   lbt1_kernel_config c = want;
@@ -687,6 +719,26 @@ hipError_t launch_step(lbt1_grid *g, const StepKernel *k, int src_parity, hipStr
   return hipLaunchKernel(k->fn, g->grid, g->block, args, 0, s);
 }
 
+// A call of n <= kBrief steps as g->brief has it.
+static hipError_t launch_brief(lbt1_grid *g, int n, hipStream_t s) {
+  const Brief &b = g->brief[n - 1];
+  for (int k = 0; k < b.times; ++k) {
+    StepArgs a{};
+    BgkArgs p{};
+    StripMap m = b.map;
+    if (g->pop)
+      p = bgk_args(g, g->parity);
+    else
+      a = step_args(g, g->parity);
+    void *args[] = {g->pop ? (void *)&p : (void *)&a, &m};
+    const hipError_t e = hipLaunchKernel(b.kern->fn, b.grid, b.block, args, 0, s);
+    if (e != hipSuccess) return e;
+    g->parity ^= 1;
+    g->steps += n / b.times;
+  }
+  return hipSuccess;
+}
+
 // A graph of kBurst / K launches (K = g->kern->steps) starting from parity p:
 // it advances burst_steps(g) steps and flips the parity once per launch.
 static const int kBurst = 64;
@@ -786,6 +838,10 @@ lbt1_status enqueue_steps(lbt1_grid *g, int64_t n, hipStream_t s, bool use_graph
     }
   }
   const int K = g->launch_steps;
+  if (n >= 1 && n <= kBrief && g->brief[n - 1].kern && !(recorded && n > 1 && g->brief[n - 1].times & 1)) {
+    if ((e = launch_brief(g, (int)n, s)) != hipSuccess) return hip_fail(e, "step launch");
+    return LBT1_OK;
+  }
   if (is_tile_kind(g->kern)) {
     // Any number of steps up to K in a launch: as few launches as K allows, with the steps
     // spread over them.  A last launch of the few steps left over would move the state for
@@ -1432,7 +1488,9 @@ lbt1_status lbt1_set_kernel(lbt1_grid *g, const lbt1_kernel_config *cfg) {
   if (st) {
     g->cfg = old;
     g->kern = oldk;
-    bind_config(g, old, g->cus);
+    const std::string said = g_err;
+    bind_config(g, g->user_cfg ? old : lbt1_kernel_config{}, g->cus);
+    g_err = said;
     return st;
   }
   g->user_cfg = cfg->kernel != LBT1_KERNEL_AUTO;

@@ -115,6 +115,18 @@ lbt1_status read_rows(const RowSource &s, uint32_t fields, size_t w, size_t rows
 
 }  // namespace lbt1
 
+namespace lbt1 {
+// How a call of very few steps runs where the library chose the grid's kernel and another one
+// takes them in less time: `times` launches of kern, which together advance them.
+struct Brief {
+  const StepKernel *kern = nullptr;
+  int times = 0;
+  StripMap map{};
+  dim3 grid{1, 1, 1}, block{1, 1, 1};
+};
+constexpr int kBrief = 2;  // most steps of such a call
+}  // namespace lbt1
+
 struct lbt1_grid {
   int device = 0, cus = 0;
   int nx = 0, ny = 0;
@@ -156,6 +168,7 @@ struct lbt1_grid {
   const lbt1::StepKernel *kern2 = nullptr;  // two-step kernel of the same strip shape, when kern takes three
   lbt1::StripMap map{};
   int launch_steps = 1;  // steps one launch of kern takes
+  lbt1::Brief brief[lbt1::kBrief];  // by steps - 1
   dim3 grid{1, 1, 1}, block{1, 1, 1};
   dim3 grid1{1, 1, 1}, block1{1, 1, 1};  // launch shape of kern1
   hipGraphExec_t burst[2] = {nullptr, nullptr};

@@ -42,10 +42,12 @@ namespace lbt1 {
 // kernel that spills or uses scratch memory)
 #define STRIP_ROWS_NOWALL(P, V) STRIP(P, false, 0, V, 6), STRIP(P, false, 0, V, 14)
 #define GATHER_ALL(P) GATHER(P, false, 0), GATHER(P, true, 0), GATHER(P, true, 1)
-// multiphase population grids (single-phase ones take the tile kernels)
-#define BGK(P, HW, W) \
-  {P, HW, W, KIND_BGK, 0, 0, (const void *)&k_bgk_step<P, HW, W>, "k_bgk_step<" #P "," #HW "," #W ">", 1, 1}
-#define BGK_ALL(P) BGK(P, false, 0), BGK(P, true, 0), BGK(P, true, 1)
+// population grids one step at a time: multiphase ones, and short calls on the others
+#define BGK(P, HW, W, SC) \
+  {P, HW, W, KIND_BGK, 0, 0, (const void *)&k_bgk_step<P, HW, W, SC>, "k_bgk_step<" #P "," #HW "," #W "," #SC ">", 1, SC}
+#define BGK_ALL(P)                                                                            \
+  BGK(P, false, 0, false), BGK(P, true, 0, false), BGK(P, true, 1, false), BGK(P, false, 0, true), \
+      BGK(P, true, 0, true), BGK(P, true, 1, true)
 // multiphase LBMTau1: gather for any geometry, strips for periodic grids without walls
 #define SC_GATHER(P, HW, W) \
   {P, HW, W, KIND_GATHER, 0, 0, (const void *)&k_step_sc_gather<P, HW, W>, "k_step_sc_gather<" #P "," #HW "," #W ">", 1, 1}

@@ -475,6 +475,54 @@ static lbt1_kernel_config sc_choice(int prec, bool haswall, int wall, int nx, in
   return best;
 }
 
+// Strips of vec columns per lane and `rows` rows of a grid, and their launch size.
+static dim3 strip_launch(int nx, int ny, int vec, int rows, int waves, int cus, StripMap *map) {
+  StripMap &m = *map;
+  m.strips_x = (chunks_of(nx, vec) + 61) / 62;  // 62 chunks of vec columns per strip
+  m.strips_y = (ny + rows - 1) / rows;
+  const int strips = m.strips_x * m.strips_y;
+  m.units = (strips + 3) / 4;
+  int blocks;
+  if (waves > 0) {
+    // `waves` wavefronts per CU, 4 per block, a multiple of 8 blocks (one range per XCD)
+    blocks = std::max(8, (cus * waves / 4) / 8 * 8);
+    blocks = std::min(blocks, (m.units + 7) / 8 * 8);
+    m.persistent = 1;
+  } else {
+    blocks = (m.units + 7) / 8 * 8;
+    m.persistent = 0;
+  }
+  m.per_xcd = (m.units + 7) / 8;
+  return dim3(blocks, 1, 1);
+}
+
+// Calls of up to three steps on periodic grids without walls, where the library chose a tile
+// kernel: strips, one launch for all the steps.  A tile's rows do not start at cache lines, and
+// few steps do not make up for it (us of a call, strips / tile): FP32 1024^2 one step 6.4 / 9.2,
+// two 8.9 / 11.5; 8192^2 one 298 / 338, two 290 / 352, three 323 / 372; FP64 1024^2 one 9.5 /
+// 12.4, two 12.8 / 15.5, 4096^2 155 / 164, 149 / 164; multiphase one step only, FP64 1024^2 11.8
+// / 14.9.  Strips of 6 rows and 2 columns a lane are the fastest, or within 2 % of it, from about
+// 700^2 nodes (16-bit storage 950^2; below, the tile kernel: FP32 512^2 two steps 5.8 / 5.9), of
+// 4 columns from 12 million nodes in FP32 and, for one step, 20 million in 16-bit storage;
+// three steps gain from 12 million nodes only.  With walls the tile kernel is the faster.
+static void brief_strips(lbt1_grid *g, int cus) {
+  const double nodes = (double)g->nx * g->ny;
+  const bool half = g->prec == LBT1_F16S || g->prec == LBT1_BF16S, f32 = g->prec == LBT1_F32;
+  if (g->haswall || nodes < (half ? 9e5 : 5e5)) return;
+  for (int n = 1; n <= (g->mp ? 1 : kBrief); ++n) {
+    const bool wide = !g->mp && nodes >= (half ? 2e7 : 1.2e7) && g->nx % 4 == 0 && (f32 || (half && n == 1));
+    if (n == 3 && !(wide && f32)) continue;
+    const int vec = wide ? 4 : 2, rows = n == 3 ? 14 : 6;
+    const StepKernel *k = find_kernel(g->prec, false, 0, KIND_STRIP, vec, rows, n, g->mp);
+    if (!k || !strip_fits(g->nx, vec, true)) continue;
+    Brief &b = g->brief[n - 1];
+    b.kern = k;
+    b.times = 1;
+    b.block = dim3(256, 1, 1);
+    b.grid = strip_launch(g->nx, g->ny, vec, rows, 0, cus, &b.map);
+  }
+}
+
 // The launch shape of a thread per node on population grids.
 static dim3 push_grid(const lbt1_grid *g) {
   const int tiles = ((g->nx + 63) / 64) * ((g->ny + 3) / 4);
@@ -493,7 +541,7 @@ static void brief_populations(lbt1_grid *g, int cus) {
   const double push = g->haswall ? 5.0 + (bytes + nodes) / 5e6 : 3.0 + bytes / 7e6;
   const dim3 grid = push_grid(g);
   if ((double)grid.x * 256 >= 4294967296.0) return;  // past what a launch takes
-  for (int n = 1; n <= kBrief; ++n) {
+  for (int n = 1; n <= 2; ++n) {
     TileMap m;
     if (!tile_map(g->nx, g->ny, g->periodic, g->cfg, n, &m)) continue;
     const bool less = push < tile_us(*g->kern, n, m.tiles, cus) && (n == 1 || nodes >= 2e5);
@@ -551,6 +599,7 @@ lbt1_status bind_config(lbt1_grid *g, const lbt1_kernel_config &want, int cus) {
     if (have) clear_error();
     c = g->mp ? sc_choice(g->prec, g->haswall, g->wall, g->nx, g->ny, g->periodic, cus)
               : default_config(g->prec, g->haswall, g->wall, g->nx, g->ny, g->periodic, cus);
+    if (is_tile(c)) brief_strips(g, cus);
   }
   const StepKernel *k = nullptr, *k1 = nullptr, *k2 = nullptr;
   if (c.kernel == LBT1_KERNEL_GATHER) {
@@ -603,24 +652,8 @@ lbt1_status bind_config(lbt1_grid *g, const lbt1_kernel_config &want, int cus) {
     g->block = dim3(64, 4, 1);
     g->grid = dim3((g->nx + 63) / 64, (g->ny + 3) / 4, 1);
   } else {
-    StripMap &m = g->map;
-    m.strips_x = (chunks_of(g->nx, c.vec) + 61) / 62;  // 62 chunks of vec columns per strip
-    m.strips_y = (g->ny + c.rows - 1) / c.rows;
-    const int strips = m.strips_x * m.strips_y;
-    m.units = (strips + 3) / 4;
-    int blocks;
-    if (c.waves > 0) {
-      // c.waves wavefronts per CU, 4 per block, a multiple of 8 blocks (one range per XCD)
-      blocks = std::max(8, (cus * c.waves / 4) / 8 * 8);
-      blocks = std::min(blocks, (m.units + 7) / 8 * 8);
-      m.persistent = 1;
-    } else {
-      blocks = (m.units + 7) / 8 * 8;
-      m.persistent = 0;
-    }
-    m.per_xcd = (m.units + 7) / 8;
     g->block = dim3(256, 1, 1);
-    g->grid = dim3(blocks, 1, 1);
+    g->grid = strip_launch(g->nx, g->ny, c.vec, c.rows, c.waves, cus, &g->map);
   }
   g->block1 = g->block;
   g->grid1 = g->grid;

@@ -124,7 +124,7 @@ struct Brief {
   StripMap map{};
   dim3 grid{1, 1, 1}, block{1, 1, 1};
 };
-constexpr int kBrief = 2;  // most steps of such a call
+constexpr int kBrief = 3;  // most steps of such a call
 }  // namespace lbt1
 
 struct lbt1_grid {

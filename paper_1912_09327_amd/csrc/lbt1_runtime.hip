@@ -438,20 +438,31 @@ static lbt1_kernel_config tile_choice(int kind, int prec, bool haswall, int wall
 // 6.5, 8192^2 125 / 168; FP64 periodic 8192^2 224 / 302, cavity 274 / 540).  16-bit
 // storage pays its codec once per step either way, and the strips exchange columns off
 // the vector ALU: on large grids whose width they take, two-step strips of 14 rows are
-// the faster (FP16S periodic 4096^2 27.3 against 29.2, cavity 8192^2 116 against 132;
-// but 2048^2 9.75 against 9.2 and 14.1 against 11.1), by a time of `half_strip` us per
-// million nodes and `half_base` us, fitted to the same grids.
+// the faster (FP16S periodic 2700 x 2500 11.7 against 13.3, 4096^2 24.6 / 30.7, 8192^2
+// 104.9 / 108.3, cavity 8192^2 116 / 133; but 2400 x 2200 11.7 / 10.6, cavity 2048^2 14.1 /
+// 10.7), and strips of 6 rows where two or three rounds of them (eight wavefronts a CU) are
+// what a periodic grid takes (BF16S 2048^2 8.55 / 9.21, FP16S 9.05 / 9.18).  Their times, in
+// us, were fitted to grids of 1200^2 to 12288^2.
 static lbt1_kernel_config default_config(int prec, bool haswall, int wall, int nx, int ny, uint32_t periodic, int cus) {
   double best_us;
   lbt1_kernel_config best = tile_choice(KIND_TILE, prec, haswall, wall, nx, ny, periodic, cus, &best_us);
-  const double half_strip = haswall ? 1.70 : 1.62, half_base = haswall ? 5.0 : 2.5;
-  if ((prec == LBT1_F16S || prec == LBT1_BF16S) && strip_fits(nx, 2, periodic & 1u) &&
-      half_strip * 1e-6 * nx * ny + half_base < best_us && find_kernel(prec, haswall, wall, KIND_STRIP, 2, 14, 2, false)) {
+  if ((prec != LBT1_F16S && prec != LBT1_BF16S) || !strip_fits(nx, 2, periodic & 1u)) return best;
+  const double nodes = (double)nx * ny;
+  const auto take = [&](int rows, double us) {
+    if (us >= best_us || !find_kernel(prec, haswall, wall, KIND_STRIP, 2, rows, 2, false)) return;
+    best_us = us;
     best = lbt1_kernel_config{};
     best.kernel = LBT1_KERNEL_STRIP;
     best.vec = 2;
-    best.rows = 14;
+    best.rows = rows;
     best.fuse = 2;
+  };
+  if (haswall) {
+    take(14, 1.70e-6 * nodes + 5.0);
+  } else {
+    if (nodes >= 6e6) take(14, 1.47e-6 * nodes + 2.6);
+    const long strips = (long)((chunks_of(nx, 2) + 61) / 62) * ((ny + 5) / 6), rounds = (strips + 8L * cus - 1) / (8L * cus);
+    if (rounds == 2 || rounds == 3) take(6, 1.6 + (prec == LBT1_F16S ? 2.45 : 2.3) * rounds);
   }
   return best;
 }

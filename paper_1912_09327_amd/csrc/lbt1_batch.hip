@@ -121,6 +121,7 @@ struct lbt1_batch {
   bool tiles = true;                        // every grid in the tile class (no strip shape asked for)
   const lbt1::BatchTileKernel *tile = nullptr;  // region shape and steps of a launch of the tile class
   int tile_steps = 8;
+  int few = 0;  // bursts of one to kFew steps are tiled for that many, longer ones (0) by choice
   bool items_dirty = true;
   hipGraphExec_t graph = nullptr;
   lbt1::GraphKey graph_key;
@@ -212,7 +213,11 @@ static GraphKey graph_key(const lbt1_batch *b, int K, int mask) {
 }
 
 // Region shape and steps per launch of the tile class: the least modelled time of a step
-// over the tiles of all resident grids.
+// over the tiles of all resident grids.  A burst of fewer steps than any choice gets a halo of
+// just those, and the regions of the longer ones: with a halo for four to ten, a burst of one
+// step and its check took 274 us on 64 cavities of 512^2 FP16S (230 on one-step strips and
+// now), 1157 on one of 8192^2 FP32 (1024, 1042 now).
+constexpr int kFew = 3;
 static void choose_tile(lbt1_batch *b) {
   double best = 1e300;
   for (int i = 0; const BatchTileKernel *t = batch_tile_kernel(b->prec, i); ++i)
@@ -240,6 +245,7 @@ static void choose_tile(lbt1_batch *b) {
         b->tile_steps = steps;
       }
     }
+  if (b->few) b->tile_steps = b->few;
 }
 
 static void rebuild_items(lbt1_batch *b) {
@@ -411,7 +417,8 @@ static lbt1_status build_graph(lbt1_batch *b, int K, int mask) {
   hipGraphNode_t partial;
   if (!st) {
     void *args[] = {&ra};
-    st = add(batch_reduce_kernel(b->prec), dim3(std::max(8, b->cus * 8)), dim3(256), args, last, nlast, &partial);
+    // (16 blocks a CU: one 8192^2 FP32 grid 510 us, 586 with 8; 64 of 512^2 FP16S 99, 115)
+    st = add(batch_reduce_kernel(b->prec), dim3(b->cus * 16), dim3(256), args, last, nlast, &partial);
   }
   if (!st) {
     void *args[] = {&ra};
@@ -455,6 +462,11 @@ static lbt1_status launch_burst(lbt1_batch *b, int K, int *nact_out) {
   *nact_out = nact;
   if (nact == 0) return LBT1_OK;
   b->h_counts[kCntActive] = nact;
+  const int few = K <= kFew ? K : 0;
+  if (few != b->few) {
+    b->few = few;
+    b->items_dirty |= b->tiles;
+  }
   const bool rebuilt = b->items_dirty;
   if (b->items_dirty) {
     rebuild_items(b);

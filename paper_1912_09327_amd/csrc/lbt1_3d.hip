@@ -76,10 +76,10 @@ struct March3 {
   int rows, threads, per_cu;  // of a block; blocks a compute unit holds
 };
 
-template <int P, int Q, bool HASWALL, int WALL, int GROUPS, int WAVES, bool FLAT = false>
+template <int P, int Q, bool HASWALL, int WALL, int GROUPS, int WAVES, int FORM = MARCH3_CHUNK>
 static March3 march3_of() {
   constexpr int RPT = 2, waves = GROUPS + march3_sides(RPT, GROUPS);
-  return {(const void *)&k_step3_march<P, Q, HASWALL, WALL, RPT, GROUPS, WAVES, FLAT>, RPT * GROUPS, 64 * waves,
+  return {(const void *)&k_step3_march<P, Q, HASWALL, WALL, RPT, GROUPS, WAVES, FORM>, RPT * GROUPS, 64 * waves,
           4 * WAVES / waves};
 }
 
@@ -91,11 +91,12 @@ static March3 march3_of() {
 // against 268 with 7 + 1; D3Q19 periodic at 128^3: 36.5 with 15 + 1 and six registers spilled,
 // 29.8 with 11 + 1).  LOW: small blocks for grids that do not fill the chip (below).  FLAT:
 // one plane (1024 x 1024 x 1: 9.9 us against 21 with the planes on both sides formed as well).
-enum March3Kind { MARCH_TALL, MARCH_LOW, MARCH_FLAT };
+enum March3Kind { MARCH_TALL, MARCH_LOW, MARCH_FLAT, MARCH_RING };
 template <int P, int Q, bool HASWALL, int WALL>
 static March3 march3_shape(March3Kind kind) {
   constexpr bool f64 = P == P_F64;
-  if (kind == MARCH_FLAT) return march3_of<P, Q, HASWALL, WALL, 7, f64 ? 3 : 4, true>();
+  if (kind == MARCH_FLAT) return march3_of<P, Q, HASWALL, WALL, 7, f64 ? 3 : 4, MARCH3_FLAT>();
+  if (kind == MARCH_RING) return march3_of<P, Q, HASWALL, WALL, 7, f64 ? 2 : 4, MARCH3_RING>();
   if constexpr (!f64) {
     if (kind == MARCH_LOW) return march3_of<P, Q, HASWALL, WALL, 7, 4>();
     return march3_of<P, Q, HASWALL, WALL, 15, 4>();
@@ -128,16 +129,16 @@ static March3 march3_kernel(int prec, int q, bool haswall, int wall, March3Kind 
 // cache level, so that nothing of a step would still be there for the next: 256^3 FP32 (268 MB)
 // 114.5 -> 111.3 us, 320^3 210 -> 204.  Below, the hint costs: 256^3 FP16S (134 MB) 82 -> 105,
 // the box of 200 x 180 x 150 FP32 (92 MB) 47 -> 58.
-static March3Map march3_map(int nx, int ny, int nz, const March3 &k, int cus, size_t state, long *planes) {
+static March3Map march3_map(int nx, int ny, int nz, const March3 &k, int cus, size_t state, bool ring, long *planes) {
   March3Map m{};
   m.tiles_x = (nx + kMarch3X - 1) / kMarch3X;
   m.tiles_y = (ny + k.rows - 3) / (k.rows - 2);
   m.oy = (ny + m.tiles_y - 1) / m.tiles_y;
   const long plane = (long)m.tiles_x * m.tiles_y, slots = (long)k.per_cu * cus;
   *planes = -1;
-  for (int chunks = 1; chunks <= nz; ++chunks) {
+  for (int chunks = 1; chunks <= (ring ? 1 : nz); ++chunks) {
     const int zc = (nz + chunks - 1) / chunks;
-    const long cost = (plane * ((nz + zc - 1) / zc) + slots - 1) / slots * (zc + 2);
+    const long cost = (plane * ((nz + zc - 1) / zc) + slots - 1) / slots * (ring ? zc : zc + 2);
     if (*planes < 0 || cost < *planes) {
       *planes = cost;
       m.zc = zc;
@@ -192,18 +193,33 @@ struct lbt1_grid3d {
 // taken where each has a compute unit to itself and forms no more planes than the tall one
 // would: 24^3 box 9.6 -> 7.6 us a step, 130 x 120 x 8 9.7 -> 8.1; with two blocks a unit they
 // gain nothing (64^3 D3Q27 9.9 against 10.1).
+//
+// The ring, which forms each plane of a periodic axis once, is taken where blocks that go through
+// all planes form fewer planes in turn than blocks of chunks do: thin grids (us a step, ring /
+// chunks: 2048 x 2048 x 2 FP32 65 / 82, FP16S 63 / 86, half-way walls D3Q27 FP16S 98 / 163; 512 x
+// 512 x 2 FP32 8.5 / 9.8, FP64 D3Q27 16.4 / 22.6; 1024 x 1024 x 8 FP16S 50 / 58; but 300 x 300 x
+// 8, in chunks of two planes, 14.4 / 11.8).  In FP32 it needs both parities in the 256 MB of the
+// last cache level: its tiles of 12 rows read 17 % more than they store, those of 28 rows 7 %
+// (2048 x 2048 x 4 FP32, 537 MB: 156 / 135; FP16S, 268 MB: 97 / 120).
 static lbt1_status bind3(lbt1_grid3d *g) {
   g->tile = g->want != LBT1_KERNEL_GATHER;
   if (g->tile) {
     auto take = [&](March3Kind kind, long *planes) {
       const March3 k = march3_kernel(g->prec, g->q, g->haswall, g->wall, kind);
-      return std::make_pair(k, march3_map(g->nx, g->ny, g->nz, k, g->cus, g->L.state, planes));
+      return std::make_pair(k, march3_map(g->nx, g->ny, g->nz, k, g->cus, g->L.state, kind == MARCH_RING, planes));
     };
-    long tall = 0, low = 0;
+    long tall = 0, low = 0, ring = 0;
     auto k = take(g->nz == 1 ? MARCH_FLAT : MARCH_TALL, &tall);
     if (g->nz > 1) {
       const auto l = take(MARCH_LOW, &low);
-      if (l.first.rows < k.first.rows && l.second.tiles <= g->cus && low <= tall) k = l;
+      if (l.first.rows < k.first.rows && l.second.tiles <= g->cus && low <= tall) {
+        k = l;
+        tall = low;
+      }
+      if (!g->haswall || (g->periodic & 4u)) {
+        const auto r = take(MARCH_RING, &ring);
+        if (ring < tall && (g->prec != LBT1_F32 || 2 * g->L.state <= (size_t)256 << 20)) k = r;
+      }
     }
     g->kern = k.first.fn;
     g->map = k.second;

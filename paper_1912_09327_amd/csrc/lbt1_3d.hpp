@@ -353,34 +353,41 @@ template <int CTRL> __device__ __forceinline__ double dpp_shift_in(double in, do
 // The same loads and stores with no arithmetic take 110-126 us, a linear copy 88.
 // D3Q19, 256^3, FP32: 128 -> 111 us a step (4.8 TB/s); D3Q27 171 -> 122; FP16S D3Q19 102 -> 82;
 // lid-driven box 200 x 180 x 150 FP32: 73 -> 50; 64^3 box 51 -> 10; 512^3 1002 -> 913.
-// Slower: grids of two to four planes (2048 x 2048 x 2, FP32: 70 -> 84 us), of which two more
-// than the grid has are formed.
 constexpr int kMarch3X = 64;  // columns of a tile
 
 // Emissions with e_x = 1 and -1 of one (e_y, e_z) share a slot.
 __device__ constexpr int k3slot[27] = {-1, 0, 0, -1, -1, -1, -1, 1, 2, 2, 1, 3, 4, 4, 3, -1, -1, -1, -1,
                                        5, 8, 6, 7, 7, 6, 8, 5};
-template <typename C, int Q, int GROUPS, int SIDES>
+// How a block goes through the planes.  CHUNK: some of them, and one more on each side.  FLAT: a
+// grid of one plane, which is its own neighbour on both sides where the axis is periodic, formed
+// once.  RING: all planes of a periodic axis, each formed once; what the first two planes send to
+// the targets that the last one completes waits in LDS (9 values a node, 13 with walls).  On thin
+// grids the two planes more that a chunk forms are much of its work: 2048 x 2048 x 2 FP32 82 us a
+// step in chunks, 65 as a ring, 512 x 512 x 2 9.8 and 8.5 (the rule is in lbt1_3d.hip).
+template <typename C, int Q, int GROUPS, int SIDES, int KEEP>
 struct March3Shared {
-  static constexpr int kCopies = sizeof(C) == 4 ? 2 : 1;
+  static constexpr int kCopies = sizeof(C) == 4 && KEEP == 0 ? 2 : 1;
   static constexpr int kVals = Q == 27 ? 6 : 4;   // of a row for the row below it, and for the row above
   C v[kCopies][2 * kVals][GROUPS * 64];
   alignas(16) C side[2][64 * SIDES][Q == 27 ? 12 : 8];  // left column, then right
   uint8_t solid[4][2][GROUPS * 64];               // by plane: SOLID bits of a wavefront's first and last row
   uint8_t edge[4][64 * SIDES];                    // by plane: SOLID bits of the halo columns
+  C keep[KEEP ? KEEP : 1][KEEP ? GROUPS * 64 : 1];  // RING: a column per thread
 };
 
 // Wavefronts for the halo columns: 32 rows each.
 constexpr int march3_sides(const int rpt, const int groups) { return (rpt * groups + 31) / 32; }
 
-template <int P, int Q, bool HASWALL, int WALL, int RPT, int GROUPS, int WAVES, bool FLAT>
+template <int P, int Q, bool HASWALL, int WALL, int RPT, int GROUPS, int WAVES, int FORM>
 __global__ void __launch_bounds__(64 * (GROUPS + march3_sides(RPT, GROUPS)), WAVES) k_step3_march(Step3Args a, March3Map m) {
   using T = Traits<P>;
   using C = typename T::C;
   using S = typename T::S;
   constexpr bool WIDE = Q == 27;
+  constexpr bool FLAT = FORM == MARCH3_FLAT, RING = FORM == MARCH3_RING;
   constexpr int SIDES = march3_sides(RPT, GROUPS);
-  using Shared = March3Shared<C, Q, GROUPS, SIDES>;
+  constexpr int KEPT = HASWALL ? 13 : 9;  // values a node keeps (RING)
+  using Shared = March3Shared<C, Q, GROUPS, SIDES, RING ? RPT * KEPT : 0>;
   __shared__ Shared sh;
   const int tile = (int)(blockIdx.x & 7) * m.per_xcd + (int)(blockIdx.x >> 3);  // XCD x: a range of tiles
   if (tile >= m.tiles) return;  // uniform across the block
@@ -395,11 +402,10 @@ __global__ void __launch_bounds__(64 * (GROUPS + march3_sides(RPT, GROUPS)), WAV
   };
 
   // The planes that are formed, from zb to ze: one more than the chunk on each side, but none
-  // outside a non-periodic axis (they send nothing).  FLAT: a grid of one plane, which is its
-  // own neighbour on both sides if the axis is periodic and is formed once.
+  // outside a non-periodic axis (they send nothing).
   const bool shut = HASWALL && !pz;
-  const int zb = FLAT ? 0 : shut ? max(z0 - 1, 0) : z0 - 1;
-  const int ze = FLAT ? 0 : shut ? min(z1, a.nz - 1) : z1;
+  const int zb = FLAT || RING ? 0 : shut ? max(z0 - 1, 0) : z0 - 1;
+  const int ze = FLAT ? 0 : RING ? a.nz - 1 : shut ? min(z1, a.nz - 1) : z1;
 
   // The emissions of a node; a SOLID node (NODE_SOLID is the one odd flag) sends zeros, which
   // is what a node with no deviation and no momentum sends.
@@ -454,15 +460,18 @@ __global__ void __launch_bounds__(64 * (GROUPS + march3_sides(RPT, GROUPS)), WAV
         put(8, f[25], f[20]);
       }
     };
+    fetch(zb);
     if constexpr (HASWALL) {
-      edge(zb, flag(zb));
+      // (all loads before the first wait)
+      const uint32_t f3 = RING ? flag(zb - 1) : 0u, f0 = flag(zb), f1 = FLAT ? 0u : flag(zb + 1), f2 = FLAT ? 0u : flag(zb + 2);
+      if (!FLAT) ahead = flag(zb + 3);
+      if (RING) edge(zb - 1, f3);
+      edge(zb, f0);
       if (!FLAT) {
-        edge(zb + 1, flag(zb + 1));
-        edge(zb + 2, flag(zb + 2));
-        ahead = flag(zb + 3);
+        edge(zb + 1, f1);
+        edge(zb + 2, f2);
       }
     }
-    fetch(zb);
     send(zb);
     fetch(min(zb + 1, ze));
     __syncthreads();
@@ -567,6 +576,29 @@ __global__ void __launch_bounds__(64 * (GROUPS + march3_sides(RPT, GROUPS)), WAV
       cy[i] = hy + mid.y;
       cm[i] = HASWALL ? hi.s + nz[i] : hi.s;
     }
+    if constexpr (RING) {
+      // plane 0 completes the last target and begins target 0 (nothing was sent up to it yet:
+      // ns ... nz hold what its walls stand for), plane 1 completes target 0
+      auto keep = [&](const int k, const C v) __attribute__((always_inline)) { sh.keep[i * KEPT + k][at] = v; };
+      if (z == 0) {
+        keep(0, lo.s);
+        keep(1, lo.x);
+        keep(2, lo.y);
+        keep(3, mid.s);
+        keep(4, mid.x);
+        keep(5, mid.y);
+        if (HASWALL) {
+          keep(9, ns[i]);
+          keep(10, nx[i]);
+          keep(11, ny[i]);
+          keep(12, nz[i]);
+        }
+      } else if (z == 1) {
+        keep(6, lo.s);
+        keep(7, lo.x);
+        keep(8, lo.y);
+      }
+    }
     C o[4] = {cs[i] + lo.s, cx[i] + lo.x, cy[i] + lo.y, cm[i] - lo.s};
     cs[i] = ns[i] + mid.s;
     cx[i] = nx[i] + mid.x;
@@ -583,10 +615,12 @@ __global__ void __launch_bounds__(64 * (GROUPS + march3_sides(RPT, GROUPS)), WAV
       o[2] *= C(a.is_j);
       o[3] *= C(a.is_j);
     }
+    const bool live = RING ? z > 1 : z > z0;
+    const int target = RING && z > a.nz ? 0 : z - 1;
     if (sizeof(S) < 8 && m.past)
-      put(std::true_type{}, z > z0, z - 1, o_at, o);
+      put(std::true_type{}, live, target, o_at, o);
     else
-      put(std::false_type{}, z > z0, z - 1, o_at, o);
+      put(std::false_type{}, live, target, o_at, o);
   };
 
 #pragma unroll
@@ -614,29 +648,44 @@ __global__ void __launch_bounds__(64 * (GROUPS + march3_sides(RPT, GROUPS)), WAV
   (void)row_bits;
   (void)nine_bits;
   if constexpr (HASWALL) {
-    uint32_t next[RPT], first[RPT + 2];
+    // RING: the plane before the first is the last one
+    const int zf = RING ? zb - 1 : zb;
+    uint32_t next[RPT], third[RPT], fourth[RPT], first[RPT + 2];  // (all loads before the first wait)
+    (void)third;
+    (void)fourth;
 #pragma unroll
     for (int i = 0; i < RPT; ++i) {
       near[i] = 0x1ffu;  // outside; a periodic axis has no target here
-      fl[i] = fetch_flag(i, zb);
-      next[i] = fetch_flag(i, zb + 1);
+      fl[i] = fetch_flag(i, zf);
+      next[i] = fetch_flag(i, zf + 1);
+      if (!FLAT) third[i] = fetch_flag(i, zf + 2);
+      if (RING) fourth[i] = fetch_flag(i, zf + 3);
     }
     __syncthreads();
 #pragma unroll
-    for (int i = 0; i < RPT; ++i) row_bits(i, zb);
+    for (int i = 0; i < RPT; ++i) row_bits(i, zf);
 #pragma unroll
     for (int i = 0; i < RPT + 2; ++i) first[i] = row[i];
     if constexpr (!FLAT) {
 #pragma unroll
       for (int i = 0; i < RPT; ++i) {
         fl[i] = next[i];
-        row_bits(i, zb + 1);
+        row_bits(i, zf + 1);
         next[i] = row[i + 1];
-        row[i + 1] = first[i + 1];
       }
+      if constexpr (RING) {
+#pragma unroll
+        for (int i = 0; i < RPT; ++i) {
+          fl[i] = third[i];
+          row_bits(i, zf + 2);
+          third[i] = row[i + 1];
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < RPT; ++i) row[i + 1] = first[i + 1];
     }
     __syncthreads();
-    nine_bits(zb);
+    nine_bits(zf);
     if constexpr (FLAT) {
 #pragma unroll
       for (int i = 0; i < RPT; ++i) {
@@ -647,9 +696,17 @@ __global__ void __launch_bounds__(64 * (GROUPS + march3_sides(RPT, GROUPS)), WAV
 #pragma unroll
       for (int i = 0; i < RPT; ++i) {
         row[i + 1] = next[i];
-        fl[i] = fetch_flag(i, zb + 2);
+        if (!RING) fl[i] = third[i];
       }
-      nine_bits(zb + 1);
+      nine_bits(zf + 1);
+      if constexpr (RING) {
+#pragma unroll
+        for (int i = 0; i < RPT; ++i) {
+          row[i + 1] = third[i];
+          fl[i] = fourth[i];
+        }
+        nine_bits(zf + 2);
+      }
     }
   } else {
     __syncthreads();
@@ -753,6 +810,27 @@ __global__ void __launch_bounds__(64 * (GROUPS + march3_sides(RPT, GROUPS)), WAV
       finish(RPT - 1, z, t[0], t[1], t[2]);
     }
     if (Shared::kCopies == 1) __syncthreads();
+  }
+  if constexpr (RING) {
+    const Plane3<C> none = {C(0), C(0), C(0)};
+    auto kept = [&](const int i, const int k) __attribute__((always_inline)) { return sh.keep[i * KEPT + k][at]; };
+#pragma unroll
+    for (int i = 0; i < RPT; ++i) {
+      if (HASWALL) {
+        held[i] <<= 1;
+        nz[i] = ns[i] + kept(i, 12);
+        ns[i] += kept(i, 9);
+        nx[i] += kept(i, 10);
+        ny[i] += kept(i, 11);
+      }
+      finish(i, a.nz, {kept(i, 0), kept(i, 1), kept(i, 2)}, {kept(i, 3), kept(i, 4), kept(i, 5)}, none);
+    }
+#pragma unroll
+    for (int i = 0; i < RPT; ++i) {
+      if (HASWALL) held[i] <<= 1;
+      finish(i, a.nz + 1, {kept(i, 6), kept(i, 7), kept(i, 8)}, none, none);
+    }
+    return;
   }
   if (!FLAT && shut && z1 == a.nz) {
     const Plane3<C> none = {C(0), C(0), C(0)};

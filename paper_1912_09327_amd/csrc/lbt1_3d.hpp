@@ -364,6 +364,7 @@ __device__ constexpr int k3slot[27] = {-1, 0, 0, -1, -1, -1, -1, 1, 2, 2, 1, 3, 
 // the targets that the last one completes waits in LDS (9 values a node, 13 with walls).  On thin
 // grids the two planes more that a chunk forms are much of its work: 2048 x 2048 x 2 FP32 82 us a
 // step in chunks, 65 as a ring, 512 x 512 x 2 9.8 and 8.5 (the rule is in lbt1_3d.hip).
+enum March3Form { MARCH3_CHUNK, MARCH3_FLAT, MARCH3_RING };
 template <typename C, int Q, int GROUPS, int SIDES, int KEEP>
 struct March3Shared {
   static constexpr int kCopies = sizeof(C) == 4 && KEEP == 0 ? 2 : 1;

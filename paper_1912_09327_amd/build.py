@@ -20,7 +20,11 @@ SOURCES = ["lbt1_kernels.hip", "lbt1_runtime.hip", "lbt1_batch.hip", "lbt1_probe
 PREC_SOURCES = ["lbt1_step_kernels.hip", "lbt1_batch_step_kernels.hip", "lbt1_tile_kernels.hip"]
 UNITS = [(s, p) for s in PREC_SOURCES for p in (1, 2, 3, 0)] + [(s, None) for s in SOURCES]
 # sources whose kernels must neither spill registers nor use scratch memory
-CHECKED = PREC_SOURCES + ["lbt1_kernels.hip"]
+CHECKED = PREC_SOURCES + ["lbt1_kernels.hip", "lbt1_3d.hip"]
+# ... except scalar registers, kept in lanes of vector registers instead of scratch memory, by
+# these kernels (a part of the mangled name: most of them): the FP64 march, whose 64-bit weights
+# take pairs of scalar registers and whose blocks of 8 wavefronts have vector ones to spare
+SGPR_SPILLS = {"k_step3_marchILi0E": 40}
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
@@ -51,6 +55,12 @@ def _resources(text):
     return res
 
 
+def spills(name, res):
+    """Whether (scratch bytes, SGPR spills, VGPR spills) of a kernel are more than it may have."""
+    allowed = max((n for part, n in SGPR_SPILLS.items() if part in name), default=0)
+    return res[0] > 0 or res[1] > allowed or res[2] > 0
+
+
 def _compile(src, prec, out, verbose):
     cmd = [HIPCC] + FLAGS + ["-c", os.path.join(CSRC, src), "-o", out]
     if prec is not None:
@@ -67,7 +77,7 @@ def _compile(src, prec, out, verbose):
         # No step kernel may spill registers or use scratch memory: the strip
         # kernels are sized to stay in registers, and a spilling variant is a
         # design error (it is not built).
-        bad = {k: v for k, v in _resources(r.stdout + r.stderr).items() if any(v)}
+        bad = {k: v for k, v in _resources(r.stdout + r.stderr).items() if spills(k, v)}
         if bad:
             raise RuntimeError("kernels spill or use scratch (scratch B/lane, SGPR, VGPR spills): "
                                + "; ".join(f"{k}: {v}" for k, v in sorted(bad.items())))

@@ -86,11 +86,12 @@ static March3 march3_of() {
 // Blocks of each storage, lattice and wall rule.  32- and 16-bit storage fits 128 registers, so
 // one block of 16 wavefronts (15 of two rows, one of halo columns) fills a compute unit: with
 // 7 + 1 wavefronts, two blocks a unit, 256^3 FP32 takes 142-155 us instead of 111, the box of
-// 200 x 180 x 150 55 instead of 48.  FP64 keeps twice the registers: 11 + 1 wavefronts (168
-// registers) where that does not spill, 7 + 1 (256) otherwise (224^3, half-way, D3Q19: 206 us
-// against 268 with 7 + 1; D3Q19 periodic at 128^3: 36.5 with 15 + 1 and six registers spilled,
-// 29.8 with 11 + 1).  LOW: small blocks for grids that do not fill the chip (below).  FLAT:
-// one plane (1024 x 1024 x 1: 9.9 us against 21 with the planes on both sides formed as well).
+// 200 x 180 x 150 55 instead of 48.  FP64 keeps twice the registers: D3Q19 takes 11 + 1
+// wavefronts (168 registers; 224^3, half-way: 206 us against 268 with 7 + 1; periodic at 128^3:
+// 36.5 with 15 + 1 and six vector registers spilled, 29.8 with 11 + 1), D3Q27 and the ring 7 + 1
+// (256 registers; with walls up to 40 scalar ones go to lanes of vector registers, no scratch).
+// LOW: small blocks for grids that do not fill the chip (below).  FLAT: one plane (1024 x 1024 x
+// 1: 9.9 us against 21 with the planes on both sides formed as well).
 enum March3Kind { MARCH_TALL, MARCH_LOW, MARCH_FLAT, MARCH_RING };
 template <int P, int Q, bool HASWALL, int WALL>
 static March3 march3_shape(March3Kind kind) {

@@ -24,7 +24,7 @@ CHECKED = PREC_SOURCES + ["lbt1_kernels.hip", "lbt1_3d.hip"]
 # ... except scalar registers, kept in lanes of vector registers instead of scratch memory, by
 # these kernels (a part of the mangled name: most of them): the FP64 march, whose 64-bit weights
 # take pairs of scalar registers and whose blocks of 8 wavefronts have vector ones to spare
-SGPR_SPILLS = {"k_step3_marchILi0E": 40}
+SGPR_SPILLS = {"k_step3_marchILi0E": 48}
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"

@@ -86,10 +86,16 @@ static March3 march3_of() {
 // Blocks of each storage, lattice and wall rule.  32- and 16-bit storage fits 128 registers, so
 // one block of 16 wavefronts (15 of two rows, one of halo columns) fills a compute unit: with
 // 7 + 1 wavefronts, two blocks a unit, 256^3 FP32 takes 142-155 us instead of 111, the box of
-// 200 x 180 x 150 55 instead of 48.  FP64 keeps twice the registers: D3Q19 takes 11 + 1
-// wavefronts (168 registers; 224^3, half-way: 206 us against 268 with 7 + 1; periodic at 128^3:
-// 36.5 with 15 + 1 and six vector registers spilled, 29.8 with 11 + 1), D3Q27 and the ring 7 + 1
-// (256 registers; with walls up to 40 scalar ones go to lanes of vector registers, no scratch).
+// 200 x 180 x 150 55 instead of 48.  FP64 keeps twice the registers:
+//   D3Q19, periodic: 15 + 1 (128 registers) or 11 + 1: 256^3 206 / 229 us, 512 x 512 x 24 94 / 86;
+//   D3Q19 with walls: 11 + 1 (168; 224^3, half-way: 206 us, 268 with 7 + 1);
+//   D3Q27, periodic: 11 + 1 or 7 + 1: 256^3 233 / 272, 200 x 180 x 8 17.1 / 14.3;
+//   D3Q27 with walls, and the ring: 7 + 1 (256, and up to 43 scalar registers go to lanes of vector
+//   registers; with 11 + 1 vector registers spill: half-way 256^3 783 us, 376 with 7 + 1).
+// Half-way walls in FP64 remain slower than the kernels before this one where those filled whole
+// rounds of blocks (D3Q19 / D3Q27 256^3 277 / 376 us against 247 / 318, 512 x 512 x 64 291 / 378
+// against 250 / 317; ragged sides are faster, 200 x 180 x 150 101 / 137 against 124 / 165), as are
+// walled grids of two to four planes by 0.5 to 3 us a step, in FP64 up to 1.7 times.
 // LOW: small blocks for grids that do not fill the chip (below).  FLAT: one plane (1024 x 1024 x
 // 1: 9.9 us against 21 with the planes on both sides formed as well).
 enum March3Kind { MARCH_TALL, MARCH_LOW, MARCH_FLAT, MARCH_RING };
@@ -101,10 +107,14 @@ static March3 march3_shape(March3Kind kind) {
   if constexpr (!f64) {
     if (kind == MARCH_LOW) return march3_of<P, Q, HASWALL, WALL, 7, 4>();
     return march3_of<P, Q, HASWALL, WALL, 15, 4>();
+  } else if constexpr (Q == 19 && !HASWALL) {
+    if (kind == MARCH_LOW) return march3_of<P, Q, HASWALL, WALL, 11, 3>();
+    return march3_of<P, Q, HASWALL, WALL, 15, 4>();
   } else if constexpr (Q == 19) {
     return march3_of<P, Q, HASWALL, WALL, 11, 3>();
   } else {
-    return march3_of<P, Q, HASWALL, WALL, 7, 2>();
+    if (HASWALL || kind == MARCH_LOW) return march3_of<P, Q, HASWALL, WALL, 7, 2>();
+    if constexpr (!HASWALL) return march3_of<P, Q, HASWALL, WALL, 11, 3>();
   }
 }
 
@@ -193,7 +203,8 @@ struct lbt1_grid3d {
 // AUTO and STRIP take k_step3_march; GATHER: the one-thread-per-node kernel.  Low blocks are
 // taken where each has a compute unit to itself and forms no more planes than the tall one
 // would: 24^3 box 9.6 -> 7.6 us a step, 130 x 120 x 8 9.7 -> 8.1; with two blocks a unit they
-// gain nothing (64^3 D3Q27 9.9 against 10.1).
+// gain nothing (64^3 D3Q27 9.9 against 10.1).  The lower blocks of FP64 are taken where they form
+// fewer rows in turn.
 //
 // The ring, which forms each plane of a periodic axis once, is taken where blocks that go through
 // all planes form fewer planes in turn than blocks of chunks do: thin grids (us a step, ring /
@@ -213,7 +224,9 @@ static lbt1_status bind3(lbt1_grid3d *g) {
     auto k = take(g->nz == 1 ? MARCH_FLAT : MARCH_TALL, &tall);
     if (g->nz > 1) {
       const auto l = take(MARCH_LOW, &low);
-      if (l.first.rows < k.first.rows && l.second.tiles <= g->cus && low <= tall) {
+      const bool less = g->prec == LBT1_F64 ? low * l.first.rows < tall * k.first.rows
+                                            : l.second.tiles <= g->cus && low <= tall;
+      if (l.first.rows < k.first.rows && less) {
         k = l;
         tall = low;
       }

@@ -176,6 +176,41 @@ template <typename C>
 struct Moments3 {
   C d, x, y, z;
 };
+// Half-way, where every node's wall sources are all on its left or all on its right (beside a wall
+// or grid edge across x, the most frequent wall there is: every row has it): the same sums with the
+// absent terms, which are zeros, left out.
+template <int Q>
+__device__ __forceinline__ constexpr uint32_t wall_column3(const int ex) {
+  uint32_t m = 0;
+  for (int q = 1; q < Q; ++q)
+    if (k3x[q] == ex) m |= wall_bit3<Q>(q);
+  return m;
+}
+template <typename C, int Q>
+__device__ __forceinline__ Moments3<C> wall_side3(const uint32_t m, const C (&f)[Q]) {
+  auto take = [&](const int l, const int r) __attribute__((always_inline)) {  // directions with e_x = 1 and -1
+    const C v = (m & wall_bit3<Q>(r)) ? f[((r - 1) ^ 1) + 1] : C(0);
+    return (m & wall_bit3<Q>(l)) ? f[((l - 1) ^ 1) + 1] : v;
+  };
+  C s[3], y[3];  // by e_z + 1
+  const C u = take(dir3<Q, 1, 1, 0>(), dir3<Q, -1, 1, 0>()), l = take(dir3<Q, 1, 0, 0>(), dir3<Q, -1, 0, 0>()),
+          w = take(dir3<Q, 1, -1, 0>(), dir3<Q, -1, -1, 0>());
+  s[1] = (u + l) + w;
+  y[1] = u - w;
+  s[2] = take(dir3<Q, 1, 0, 1>(), dir3<Q, -1, 0, 1>());
+  s[0] = take(dir3<Q, 1, 0, -1>(), dir3<Q, -1, 0, -1>());
+  y[2] = y[0] = C(0);
+  if constexpr (Q == 27) {
+    const C bu = take(dir3<Q, 1, 1, 1>(), dir3<Q, -1, 1, 1>()), bw = take(dir3<Q, 1, -1, 1>(), dir3<Q, -1, -1, 1>());
+    const C tu = take(dir3<Q, 1, 1, -1>(), dir3<Q, -1, 1, -1>()), tw = take(dir3<Q, 1, -1, -1>(), dir3<Q, -1, -1, -1>());
+    s[2] = (bu + s[2]) + bw;
+    y[2] = bu - bw;
+    s[0] = (tu + s[0]) + tw;
+    y[0] = tu - tw;
+  }
+  const C d = (s[2] + s[1]) + s[0];
+  return {d, (m & wall_column3<Q>(1)) ? d : -d, (y[2] + y[1]) + y[0], s[2] - s[0]};
+}
 template <typename C, int Q, int WALL>
 __device__ __forceinline__ Moments3<C> wall3(const uint32_t m, const C d, const C (&f)[Q]) {
   if constexpr (WALL == WALL_PAPER) {
@@ -185,6 +220,8 @@ __device__ __forceinline__ Moments3<C> wall3(const uint32_t m, const C d, const 
             C(wall_weight3<Q, 2, 1, 2>(m) - wall_weight3<Q, 2, -1, 2>(m)) * u,
             C(wall_weight3<Q, 2, 2, 1>(m) - wall_weight3<Q, 2, 2, -1>(m)) * u};
   } else {
+    constexpr uint32_t L = wall_column3<Q>(1), R = wall_column3<Q>(-1);
+    if (!__any((m & wall_bits3<Q>() & ~(L | R)) || ((m & L) && (m & R)))) return wall_side3<C, Q>(m, f);
     C v[Q];
     auto take = [&](const int ez) __attribute__((always_inline)) {  // one e_z at a time, for the registers' sake
       if (sizeof(C) == 8) __builtin_amdgcn_sched_barrier(0);
@@ -727,8 +764,12 @@ __global__ void __launch_bounds__(64 * (GROUPS + march3_sides(RPT, GROUPS)), WAV
       source(raw[i], HASWALL ? near[i] >> 13 & 1u : 0u, f);
       if constexpr (HASWALL) {
         nz[i] = ns[i];
-        if (near[i] & wall_bits3<Q>()) {
-          const Moments3<C> w = wall3<C, Q, WALL>(near[i], dec3_d<P>(a, raw[i][0]), f);
+        // (half-way: a SOLID node takes nothing in, and its neighbours would send the lanes beside it
+        // the long way)
+        const uint32_t walls =
+            WALL == WALL_HALFWAY && (near[i] >> 13 & 1u) ? 0u : near[i] & wall_bits3<Q>();
+        if (walls) {
+          const Moments3<C> w = wall3<C, Q, WALL>(walls, dec3_d<P>(a, raw[i][0]), f);
           ns[i] += w.d;
           nx[i] += w.x;
           ny[i] += w.y;

@@ -22,5 +22,5 @@ def test_every_kernel_source_is_checked():
 def test_what_the_check_refuses():
     for name in (FP32_MARCH, "11k_step_tileILi1E"):
         assert not _bad(name) and _bad(name, scratch=4) and _bad(name, sgpr=1) and _bad(name, vgpr=1)
-    assert not _bad(FP64_MARCH, sgpr=40)
-    assert _bad(FP64_MARCH, sgpr=41) and _bad(FP64_MARCH, sgpr=1, vgpr=1) and _bad(FP64_MARCH, scratch=4)
+    assert not _bad(FP64_MARCH, sgpr=48)
+    assert _bad(FP64_MARCH, sgpr=49) and _bad(FP64_MARCH, sgpr=1, vgpr=1) and _bad(FP64_MARCH, scratch=4)

@@ -290,7 +290,8 @@ lbt1_status lbt1_set_kernel(lbt1_grid *g, const lbt1_kernel_config *cfg);
  * symbol-like name, NUL-terminated, at most name_cap bytes. */
 lbt1_status lbt1_get_kernel(lbt1_grid *g, lbt1_kernel_config *cfg, char *name, size_t name_cap);
 
-/* Time every built configuration that fits this grid, on the grid's own memory
+/* Time every built configuration that fits this grid (of the region shapes those
+ * whose modelled time is within half of the least), on the grid's own memory
  * (its state is saved to scratch memory first and restored afterwards):
  * `steps` steps each, best of `reps`; then those within 5 % of the fastest (at
  * most eight) again as lbt1_step runs them, in graph bursts of 64 steps (three
@@ -336,7 +337,7 @@ lbt1_status lbt1_grid3d_create(const lbt1_grid3d_desc *d, lbt1_grid3d **out);
 /* Flags (NULL: all FLUID) and moments (NULL: rho = 1, j = 0); validation as 2-D. */
 lbt1_status lbt1_grid3d_set_geometry(lbt1_grid3d *g, const uint8_t *flags, const double *rho, const double *jx,
                                      const double *jy, const double *jz);
-/* n steps, asynchronous (one launch per step, one thread per node). */
+/* n steps, asynchronous (one launch per step). */
 lbt1_status lbt1_grid3d_step(lbt1_grid3d *g, int64_t n);
 /* rho and momentum into nz*ny*nx host arrays (any may be NULL); synchronises. */
 lbt1_status lbt1_grid3d_read_moments(lbt1_grid3d *g, double *rho, double *jx, double *jy, double *jz);
@@ -344,13 +345,11 @@ lbt1_status lbt1_grid3d_read_moments(lbt1_grid3d *g, double *rho, double *jx, do
  * 4 residual max |u - u_snap| (LBT1_REDUCE_RESIDUAL, refreshes the snapshot),
  * 5 non-finite count, 6 FLUID count, 7 zero.  Synchronises. */
 lbt1_status lbt1_grid3d_reduce(lbt1_grid3d *g, uint32_t what, double *out);
-/* Kernel family: LBT1_KERNEL_AUTO (default) and LBT1_KERNEL_STRIP take the tile
- * kernel (a block of 8 rows marches along z with three planes of per-node
- * values in LDS: a wavefront holds 64 targets of a row and the block a halo
- * ring, with the flags in LDS on grids with SOLID or FIXED nodes or a
- * non-periodic axis; for D3Q27 on grids with every axis periodic and no SOLID
- * or FIXED node, 62 targets and 2 halo columns, the x neighbours taken by lane
- * shifts); LBT1_KERNEL_GATHER one thread per node.  They give the same bits.
+/* Kernel family: LBT1_KERNEL_AUTO (default) and LBT1_KERNEL_STRIP take the
+ * marching kernel (a block goes along z through the planes of a tile of 64
+ * columns and 12 to 28 rows: every node's emissions are formed once, moved to
+ * their targets' columns by lane shifts and summed in registers as the planes
+ * pass); LBT1_KERNEL_GATHER one thread per node.  They give the same bits.
  * get_kernel reports the family bound (ESTATE before set_geometry). */
 lbt1_status lbt1_grid3d_set_kernel(lbt1_grid3d *g, int32_t kernel);
 lbt1_status lbt1_grid3d_get_kernel(lbt1_grid3d *g, int32_t *kernel);
@@ -435,7 +434,7 @@ typedef struct {
 lbt1_status lbt1_batch_set_shape(lbt1_batch *b, const lbt1_batch_shape *shape);
 
 /* The fuse mode, LDS mode and column cap in force and the strip heights the resident
- * grids run with now. */
+ * grids run with now (all 0 under the default shape, which has no strips). */
 lbt1_status lbt1_batch_get_shape(lbt1_batch *b, lbt1_batch_shape *shape);
 
 /* Time tile shapes on the resident, running grids and keep the fastest: each fuse

@@ -1609,9 +1609,13 @@ lbt1_status lbt1_autotune(lbt1_grid *g, int32_t steps, int32_t reps, lbt1_kernel
           cands.push_back(c);
         }
   {
+    // tile kernels whose modelled time is within half of the least (the model is off by up to a
+    // quarter; the others would be most of the time the tuning takes, 2.1 s of it at 8192^2 FP32)
     const int kind = g->mp ? KIND_SC_TILE : KIND_TILE;
     int nk = 0;
     const StepKernel *tk = step_kernels(&nk);
+    double least = 0;
+    (void)tile_choice(kind, g->prec, g->haswall, g->wall, g->nx, g->ny, g->periodic, g->cus, &least);
     for (int i = 0; i < nk; ++i) {
       if (tk[i].kind != kind || tk[i].prec != g->prec || (tk[i].haswall != 0) != g->haswall ||
           (g->haswall && tk[i].wall != g->wall))
@@ -1624,7 +1628,8 @@ lbt1_status lbt1_autotune(lbt1_grid *g, int32_t steps, int32_t reps, lbt1_kernel
         c.rows = tk[i].rows;
         c.waves = tk[i].threads / 64;
         c.fuse = f;
-        if (tile_map(g->nx, g->ny, g->periodic, c, f, &m, reach_of(kind))) cands.push_back(c);
+        if (tile_map(g->nx, g->ny, g->periodic, c, f, &m, reach_of(kind)) && tile_us(tk[i], f, m.tiles, g->cus) <= 1.5 * least)
+          cands.push_back(c);
       }
     }
   }

@@ -12,9 +12,11 @@ The JSON line carries:
   value        fluid lattice updates per second (MLUPS), whole job
   roofline     the step kernel's algorithmic HBM bytes per launch (read and write
                3 moment planes once: 2 * 3 * c bytes per fluid node, for one step,
-               or for two when the kernel fuses two steps per pass) over its
+               or for the several steps of a launch) over its
                average launch duration from HIP events on the grid's stream,
-               against 8 TB/s
+               against 8 TB/s: achieved, peak and frac; bound names the ceiling the
+               kernel is nearer to, hbm or valu (alu: vector-ALU issue; counted figures
+               where the committed counter summaries have this kernel)
   cpu_baseline the FP64 CPU oracle on a bounded sample of the same workload
   variants     the same run with FP64, FP16 and BF16 shifted storage, each with its
                error against the FP64 run
@@ -201,16 +203,25 @@ def kernel_source_hash():
     return h.hexdigest()[:16]
 
 
+def tile_source_hash():
+    """Hash of the sources that define the tile kernels' code beyond kernel_source_hash's."""
+    h = hashlib.sha256()
+    for f in ("lbt1_tile.hpp", "lbt1_tile_args.hpp"):
+        h.update(open(os.path.join(ROOT, "paper_1912_09327_amd", "csrc", f), "rb").read())
+    return h.hexdigest()[:16]
+
+
 def profile_record(name, storage, kernel_name):
     """The record of `kernel_name` for `storage` in a committed counter summary
-    (one record, or a list of them for several strip shapes), if it was taken on
+    (one record, or a list of them for several kernels), if it was taken on
     these kernel sources; None otherwise."""
     try:
         recs = json.load(open(os.path.join(ROOT, "profiles", name)))[storage]
     except (OSError, KeyError, ValueError):
         return None
     for rec in recs if isinstance(recs, list) else [recs]:
-        if rec.get("source_hash") == kernel_source_hash() and rec.get("kernel_bench") == kernel_name:
+        if (rec.get("source_hash") == kernel_source_hash() and rec.get("kernel_bench") == kernel_name
+                and ("tile_hash" not in rec or rec["tile_hash"] == tile_source_hash())):
             return rec
     return None
 
@@ -404,6 +415,8 @@ def run_periodic(args, torch):
         alu["counted_frac"] = round(counted / launch_s / 1e12 / VALU_PEAK_TOPS, 4)
         alu["counted_ops_per_lup"] = round(counted / lups_launch, 2)
     line["roofline"]["alu"] = alu
+    if alu.get("counted_frac", alu["frac"]) > (line["roofline"]["traffic"] or head["achieved"]) / HBM_PEAK_GBPS:
+        line["roofline"]["bound"] = "valu"
     try:
         cc = copy_ceiling()
         line["roofline"]["copy_ceiling_GBps"] = round(cc, 1)

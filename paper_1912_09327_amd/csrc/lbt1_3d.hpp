@@ -380,16 +380,17 @@ template <int CTRL> __device__ __forceinline__ double dpp_shift_in(double in, do
 // moments, so that a node knows the 26 nodes around it when its emissions are formed, and
 // what the wall rule puts in the place of its SOLID sources comes from these emissions.
 //
-// Why this shape.  It replaces kernels in which every target formed its Q arrivals from three
-// planes in LDS: 210 vector operations and 44 LDS instructions a node for D3Q19, now 115 and
-// 8 for every other row.  What bounds it then is the memory system, not the arithmetic (60 %
-// of the issue slots at 256^3): rows that are read by two tiles cost, so tiles are tall (28
-// rows: 114 us a step at 256^3 FP32, 26 rows 123, 19 rows 131, 12 rows 155), and loads and
-// stores that start between cache lines cost, so tiles are 64 aligned columns and the columns
-// next to them have a wavefront of their own (62 columns of 64 lanes, without it: 139-158).
-// The same loads and stores with no arithmetic take 110-126 us, a linear copy 88.
-// D3Q19, 256^3, FP32: 128 -> 111 us a step (4.8 TB/s); D3Q27 171 -> 122; FP16S D3Q19 102 -> 82;
-// lid-driven box 200 x 180 x 150 FP32: 73 -> 50; 64^3 box 51 -> 10; 512^3 1002 -> 913.
+// Why this shape.  It replaces kernels in which every target formed its Q arrivals from
+// three planes in LDS: 210 vector operations and 44 LDS instructions a node for D3Q19, now
+// 118 and 6 a node formed, halo wavefront included (146 and 7 a node stored at 256^3).  What
+// bounds it then is the memory system, not the arithmetic (50 % of the issue rate at 256^3):
+// rows that are read by two tiles cost, so tiles are tall (28 rows: 114 us a step at 256^3
+// FP32, 26 rows 123, 19 rows 131, 12 rows 155), and loads and stores that start between
+// cache lines cost, so tiles are 64 aligned columns and the columns next to them have a
+// wavefront of their own (62 columns of 64 lanes, without it: 139-158). The same loads and
+// stores with no arithmetic take 110-126 us, a linear copy 88. D3Q19, 256^3, FP32: 128 ->
+// 111 us a step (4.8 TB/s); D3Q27 171 -> 122; FP16S D3Q19 102 -> 82; lid-driven box 200 x
+// 180 x 150 FP32: 73 -> 50; 64^3 box 51 -> 10; 512^3 1002 -> 913.
 constexpr int kMarch3X = 64;  // columns of a tile
 
 // Emissions with e_x = 1 and -1 of one (e_y, e_z) share a slot.

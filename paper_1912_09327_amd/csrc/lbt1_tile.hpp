@@ -20,10 +20,11 @@
 //
 // Small grids are bound by the launch (256^2 FP32 cavity: 7.2 us for 8 steps, 4 us of it
 // the launch; 2.87 us per step before, 0.91 now), large ones by vector-ALU issue: the
-// wall-free step is 44 vector instructions a node, and a 128 x 64 region at 6 steps
-// stores 74 % of what it computes (4096^2 FP32: 28.8 us per step, about 94 % of the
-// issue rate, against 34.2 with three-step strips, which wait for memory at two
-// wavefronts per SIMD).
+// wall-free step is 46 vector instructions a node, and a 128 x 64 region at 6 steps
+// stores 73 % of what it computes (8192^2 FP32: 398 million vector instructions in the
+// 669 us of 6 steps, 97 % of the issue rate, and 1.82 GB, 2.7 TB/s; 4096^2: 28.8 us per
+// step, against 34.2 with three-step strips, which wait for memory at two wavefronts
+// per SIMD).
 #pragma once
 #include "lbt1_tile_args.hpp"
 #include "lbt1_device.hpp"
